@@ -189,6 +189,15 @@ __device__ void chk_tile(const ProblemDesc& D, const ProblemIO& io, int b, doubl
 // ---------------------------------------------------------------------------
 // device: one tile of one pass of one problem
 #define PSV_BX_SIZES(X) X(16) X(24) X(32) X(48) X(64) X(96) X(128)
+inline bool bx_compiled(int M) {
+    switch (M) {
+#define PSV_CASE(n) case n:
+        PSV_BX_SIZES(PSV_CASE)
+#undef PSV_CASE
+        return true;
+        default: return false;
+    }
+}
 
 template <typename T, int MODE, bool STAGE>
 __device__ __forceinline__ void run_fwd_s(const ProblemDesc& D, const FwdArgs& a, int b,
@@ -504,8 +513,10 @@ void plan_free(Plan& p);
 static size_t kind_lds(const Plan& p, int kind, bool fp32) {
     const size_t cs = fp32 ? sizeof(float2) : sizeof(double2);
     switch (kind) {
-        case K_FWD: case K_RES: return fwd_x_lds(make_xgeom(p), cs);
-        case K_INV: case K_INVADD: return inv_x_lds(make_xgeom(p, true), cs);
+        case K_FWD: case K_RES:
+            return fwd_x_lds(make_xgeom(p), cs, kind == K_RES ? FWD_RESID : p.opts.method == PSV_SPLIT_RHO0 ? FWD_METHOD1 : FWD_CONST,
+                             bx_compiled(p.nx / 2));
+        case K_INV: case K_INVADD: return inv_x_lds(make_xgeom(p, true), cs, bx_compiled(p.nx / 2));
         case K_Y: case K_YI: return yz_lds(p.ny, p.lp.kc, cs);
         case K_Z: case K_Z2: return ifc_lds(p);
         default: return 0;

@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace psv {
 
 template <typename T> struct V2;
@@ -31,6 +33,36 @@ __device__ __forceinline__ C cmul_i(C a) {
 
 template <typename D, typename S>
 __device__ __forceinline__ D cconv(S a) { return D{(decltype(D::x))a.x, (decltype(D::x))a.y}; }
+
+// Division of an index below 2^31 by a divisor known on the host: one
+// multiply-high and a shift (m = ceil(2^(31+s) / d), s = ceil(log2 d), has an
+// error below d 2^-s <= 1 in the product, so the quotient is exact), where a
+// division by a kernel argument compiles to about 25 instructions.
+struct FastDiv {
+    unsigned d, m;
+    int s;  // -1: d = 1
+};
+inline FastDiv fast_div(int d) {
+    FastDiv f{(unsigned)d, 0u, -1};
+    if (d <= 1) return f;
+    int s = 0;
+    while ((1ll << s) < d) ++s;
+    f.m = (unsigned)(((1ull << (31 + s)) + d - 1) / d);
+    f.s = s - 1;
+    return f;
+}
+__device__ __forceinline__ int fdiv(int n, const FastDiv& f) {
+    return f.s < 0 ? n : (int)(__umulhi((unsigned)n, f.m) >> f.s);
+}
+
+// Element i of an array that is uniform over the block, through a 32-bit byte
+// offset (i sizeof(T) < 2^32): the address is a scalar base and one vector
+// register, with no 64-bit vector arithmetic.
+template <typename T>
+__device__ __forceinline__ T& at_off(T* base, unsigned i) {
+    using B = std::conditional_t<std::is_const<T>::value, const char, char>;
+    return *reinterpret_cast<T*>(reinterpret_cast<B*>(base) + i * (unsigned)sizeof(T));
+}
 
 // Radix sequence of one FFT length (product of r[0..count-1] = n).
 struct Radices {
@@ -203,6 +235,14 @@ struct Pad8 {
     __host__ __device__ static constexpr int step(int s) { return s + s / 8; }
 };
 
+template <int R, int DIR, typename C>
+__device__ __forceinline__ void bfly_ct(C* v) {
+    if (R == 2) bfly2<DIR>(v);
+    if (R == 3) bfly3<DIR>(v);
+    if (R == 4) bfly4<DIR>(v);
+    if (R == 8) bfly8<DIR>(v);
+}
+
 // Butterfly j of a radix-R Stockham stage (NS = product of the earlier
 // radices, NB = N / R) of the line starting at element off: load with
 // twiddles and transform into v, then store.
@@ -226,15 +266,12 @@ __device__ __forceinline__ void stockham_load_ct(const C* __restrict__ in, int j
             v[r] = cmul(v[r], w);
         }
     }
-    if (R == 2) bfly2<DIR>(v);
-    if (R == 3) bfly3<DIR>(v);
-    if (R == 4) bfly4<DIR>(v);
-    if (R == 8) bfly8<DIR>(v);
+    bfly_ct<R, DIR>(v);
 }
 
-// A8: off is a multiple of 8 (lines of a length divisible by 8), so in a
-// first stage (NS = 1) with R dividing 8 the R outputs of a butterfly stay in
-// one group of 8 elements.
+// A8: off is a multiple of 8 (lines of a length divisible by 8), so in an
+// early stage (NS dividing 8) the outputs of a butterfly are constant offsets
+// apart.
 template <int R, int NS, typename P = NoPad, bool A8 = false, typename C>
 __device__ __forceinline__ void stockham_store_ct(C* __restrict__ out, int j, const C* v,
                                                   int off = 0) {
@@ -243,6 +280,12 @@ __device__ __forceinline__ void stockham_store_ct(C* __restrict__ out, int j, co
         const int b = P::at(base);
 #pragma unroll
         for (int r = 0; r < R; ++r) out[b + r * P::step(NS)] = v[r];
+    } else if constexpr (A8 && 8 % NS == 0 && (NS * R) % 8 == 0) {
+        // base mod 8 is below NS, so no output crosses a group of 8 by its
+        // own offset: at(base + r NS) = at(base) + at(r NS)
+        const int b = P::at(base);
+#pragma unroll
+        for (int r = 0; r < R; ++r) out[b + P::at(r * NS)] = v[r];
     } else if constexpr (A8 && NS == 1 && 8 % R == 0) {
         const int b = P::at(base);
 #pragma unroll
@@ -253,46 +296,73 @@ __device__ __forceinline__ void stockham_store_ct(C* __restrict__ out, int j, co
     }
 }
 
-// Two-buffer variant: stage S reads src and writes dst (both in layout P,
-// line l starting at element l * lstride, lstride a multiple of 8 when N is),
-// then the buffers swap. Returns the buffer holding the result; ends with the
-// block synchronised.
-template <int N, int S, int DIR, int TWM, typename P = NoPad, typename C>
-__device__ __forceinline__ C* fft_stages(C* src, C* dst, int nlines, int lstride,
-                                         const C* __restrict__ tw) {
-    constexpr RadixList RL = radix_list(N);
-    if constexpr (S == RL.count) {
-        return src;
-    } else {
-        constexpr int R = RL.r[S];
-        constexpr int NS = radix_prefix(RL, S);
-        constexpr int NB = N / R;
-        constexpr int TSTEP = (N / (NS * R)) * TWM;
-        const int total = nlines * NB;
-        for (int t = threadIdx.x; t < total; t += 256) {
-            const int line = t / NB;
-            const int j = t - line * NB;
-            C v[R];
-            stockham_load_ct<R, DIR, NS, NB, TSTEP, P>(src, j, tw, v, line * lstride);
-            stockham_store_ct<R, NS, P, N % 8 == 0>(dst, j, v, line * lstride);
-        }
-        __syncthreads();
-        return fft_stages<N, S + 1, DIR, TWM, P>(dst, src, nlines, lstride, tw);
+// ---- FFT stages over several lines of compile-time length N, line l at
+// element l * ls of a buffer in layout P, tables of N twiddles
+// exp(-2 pi i t / N). The stages of a transform are a radix list read from
+// entry S on, with NS the product of the radices already applied (a caller may
+// have applied the first ones itself, from registers).
+
+// radix_list with the pair 8, 2 written as 4, 4 (as many stages, with more
+// butterflies to share among the threads in each)
+__host__ __device__ constexpr RadixList radix_list_44(int n) {
+    RadixList L = radix_list(n);
+    for (int i = 0; i + 1 < L.count; ++i)
+        if (L.r[i] == 8 && L.r[i + 1] == 2) L.r[i] = L.r[i + 1] = 4;
+    return L;
+}
+// Radices of a length N whose first radix-2 stage is applied apart.
+template <int N>
+struct AfterRadix2 {
+    static constexpr RadixList list = radix_list_44(N / 2);
+};
+template <int N>
+struct AllRadices {
+    static constexpr RadixList list = radix_list(N);
+};
+
+// One stage over nlines lines, src to dst (NT threads); the caller synchronises.
+template <int N, int R, int NS, int DIR, int NT, typename P, typename C>
+__device__ __forceinline__ void line_stage(const C* src, C* dst, int nlines, int ls,
+                                           const C* __restrict__ tw) {
+    constexpr int NB = N / R;
+    const int total = nlines * NB;
+    for (int t = threadIdx.x; t < total; t += NT) {
+        const int line = t / NB;
+        const int j = t - line * NB;
+        C v[R];
+        stockham_load_ct<R, DIR, NS, NB, N / (NS * R), P>(src + line * ls, j, tw, v);
+        stockham_store_ct<R, NS, P, N % 8 == 0>(dst + line * ls, j, v);
     }
 }
 
-// In-place variant for NL lines of length N stored one after the other in
-// one LDS buffer in layout P: every stage reads all of its butterflies into
-// registers (a thread takes butterflies t, t + 256, ...), waits for the block,
-// then writes. Ends with the block synchronised.
-template <int N, int S, int DIR, int TWM, int NL, typename P = NoPad, typename C>
+// Stages S .. END - 1 of List, ping-ponging between src and dst with a barrier
+// after each; returns the buffer with the result.
+template <int N, typename List, int S, int END, int NS, int DIR, int NT, typename P, typename C>
+__device__ __forceinline__ C* line_stages(C* src, C* dst, int nlines, int ls,
+                                          const C* __restrict__ tw) {
+    if constexpr (S >= END) {
+        return src;
+    } else {
+        constexpr int R = List::list.r[S];
+        line_stage<N, R, NS, DIR, NT, P>(src, dst, nlines, ls, tw);
+        __syncthreads();
+        return line_stages<N, List, S + 1, END, NS * R, DIR, NT, P>(dst, src, nlines, ls, tw);
+    }
+}
+
+// In-place variant, stages S .. END - 1 of radix_list(N), for NL lines of
+// length N stored one after the other in one LDS buffer in layout P: every
+// stage reads all of its butterflies into registers (a thread takes
+// butterflies t, t + 256, ...), waits for the block, then writes. Ends with
+// the block synchronised.
+template <int N, int S, int END, int DIR, int NL, typename P = NoPad, typename C>
 __device__ __forceinline__ void fft_inplace(C* buf, const C* __restrict__ tw) {
     constexpr RadixList RL = radix_list(N);
-    if constexpr (S < RL.count) {
+    if constexpr (S < END) {
         constexpr int R = RL.r[S];
         constexpr int NS = radix_prefix(RL, S);
         constexpr int NB = N / R;
-        constexpr int TSTEP = (N / (NS * R)) * TWM;
+        constexpr int TSTEP = N / (NS * R);
         constexpr int TOTAL = NL * NB;
         constexpr int IT = (TOTAL + 255) / 256;
         C v[IT][R];
@@ -314,7 +384,7 @@ __device__ __forceinline__ void fft_inplace(C* buf, const C* __restrict__ tw) {
             }
         }
         __syncthreads();
-        fft_inplace<N, S + 1, DIR, TWM, NL, P>(buf, tw);
+        fft_inplace<N, S + 1, END, DIR, NL, P>(buf, tw);
     }
 }
 
@@ -332,18 +402,6 @@ __device__ __forceinline__ double rcp_nr(double s) {
 __device__ __forceinline__ double rcp_nr1(double s) {
     const double r = __builtin_amdgcn_rcp(s);
     return fma(r, fma(-s, r, 1.0), r);
-}
-
-// N = 0 selects the runtime-length routine above (layout P applies to N > 0
-// only; the runtime routine reads and writes unpadded lines).
-template <int N, int DIR, int TWM, typename P = NoPad, typename C>
-__device__ __forceinline__ C* lds_fft_n(C* buf0, C* buf1, int L, int nlines, int lstride,
-                                        const Radices& rp, const C* __restrict__ tw) {
-    if constexpr (N > 0) {
-        return fft_stages<N, 0, DIR, TWM, P>(buf0, buf1, nlines, lstride, tw);
-    } else {
-        return lds_fft<DIR>(buf0, buf1, L, nlines, lstride, rp, tw, L * TWM);
-    }
 }
 
 // Block copy of n elements (256 threads), G per thread in flight: get(t) is
@@ -478,9 +536,9 @@ __device__ __forceinline__ int xcd_remap(int b, int nb) {
 // y neighbours come from another XCD only at the window's two edges. (With
 // contiguous plane ranges an XCD works on about two planes at once and the
 // neighbouring planes of p and rho leave its L2 between their uses.)
-__device__ __forceinline__ int xcd_windows(int b, int w, int tiles) {
+__device__ __forceinline__ int xcd_windows(int b, int w, int tiles, const FastDiv& by_w) {
     const int x = b & 7, i = b >> 3;
-    const int k = i / w;
+    const int k = fdiv(i, by_w);
     return k * tiles + x * w + (i - k * w);
 }
 

@@ -268,6 +268,7 @@ __global__ void k_set_scalar(double* dst, double v) {
 
 struct Geo {
     int nx, ny, nz;
+    FastDiv by_win;  // adjoint faces: division by a window's blocks per plane
     double inv_dx, inv_dy;
     const double* inv_h;
     const double* inv_g;
@@ -457,7 +458,7 @@ __global__ void __launch_bounds__(RB) k_adjoint_faces(Geo g, AdjArgs a) {
     // contiguous range
     const unsigned tpp = plane2 / RB;  // blocks per plane
     const bool win = plane2 % RB == 0 && tpp % 8 == 0 && gridDim.x * RB == npair;
-    const unsigned bx = win ? (unsigned)xcd_windows((int)blockIdx.x, (int)(tpp / 8), (int)tpp)
+    const unsigned bx = win ? (unsigned)xcd_windows((int)blockIdx.x, (int)(tpp / 8), (int)tpp, g.by_win)
                             : (unsigned)xcd_remap((int)blockIdx.x, (int)gridDim.x);
     // x neighbours from the adjacent lanes where a wave holds whole lines (M
     // divides 64) or 64 pairs of one line (64 divides M; the wave's first and
@@ -629,6 +630,7 @@ Geo make_geo(const Plan& p) {
     g.nx = p.nx;
     g.ny = p.ny;
     g.nz = p.nz;
+    g.by_win = fast_div(std::max(1, p.nx / 2 * p.ny / RB / 8));
     g.inv_dx = 1.0 / p.dx;
     g.inv_dy = 1.0 / p.dy;
     g.inv_h = p.t.inv_h;

@@ -15,7 +15,7 @@ __global__ void __launch_bounds__(256) k_fwd_x(XGeom g, Stencil st, FwdArgs a,
     extern __shared__ __align__(16) unsigned char smem_raw[];
     __shared__ double red[16];
     if (a.done && *a.done) return;
-    const int b = g.win ? xcd_windows(blockIdx.x, g.win, g.tiles) : xcd_remap(blockIdx.x, gridDim.x);
+    const int b = g.win ? xcd_windows(blockIdx.x, g.win, g.tiles, g.by_win) : xcd_remap(blockIdx.x, gridDim.x);
     fwd_x_tile<TC, TS, MODE, N, STAGE>(g, st, a, tw_g, spec, b, smem_raw, red);
 }
 
@@ -34,7 +34,7 @@ __global__ void __launch_bounds__(256) k_fwd_x_capped(XGeom g, Stencil st, FwdAr
     if (a.done && *a.done) return;
     const int nt = g.tiles * g.nz;
     for (int v = blockIdx.x; v < nt; v += gridDim.x) {
-        const int b = g.win ? xcd_windows(v, g.win, g.tiles) : xcd_remap(v, nt);
+        const int b = g.win ? xcd_windows(v, g.win, g.tiles, g.by_win) : xcd_remap(v, nt);
         fwd_x_tile<TC, TS, MODE, N, STAGE>(g, st, a, tw_g, spec, b, smem_raw, red);
         if (v + (int)gridDim.x < nt) __syncthreads();  // the next tile reuses the LDS
     }
@@ -75,13 +75,10 @@ inline int x_grid(int nt, int max_blocks) {
     return std::max(8, max_blocks / 8 * 8);
 }
 
-// x-line lengths with a compile-time FFT (M = nx/2); others use the runtime one
-#define PSV_X_SIZES(X) X(16) X(24) X(32) X(48) X(64) X(96) X(128) X(192) X(256) X(512)
-
 template <typename TC, typename TS, int MODE, int N, bool STAGE>
 void fwd_launch_s(const Plan& p, const XGeom& g, const Stencil& st, const FwdArgs& a,
                   const c2<TC>* tw, hipStream_t s) {
-    const size_t lds = fwd_x_lds(g, sizeof(c2<TC>), MODE);
+    const size_t lds = fwd_x_lds(g, sizeof(c2<TC>), MODE, N > 0);
     allow_lds(k_fwd_x<TC, TS, MODE, N, STAGE>, lds);
     const int nt = g.tiles * p.nz, grid = x_grid(nt, a.max_blocks);
     // capped grids only for the FP32 refinement residual, the one pass that
@@ -130,7 +127,7 @@ void fwd_impl(const Plan& p, const FwdArgs& a, hipStream_t s) {
 template <typename TC, typename TS, int MODE, int N>
 void inv_launch(const Plan& p, const XGeom& g, const c2<TC>* tw, double* out, double scale,
                 const int* done, hipStream_t s, int max_blocks) {
-    const size_t lds = inv_x_lds(g, sizeof(c2<TC>));
+    const size_t lds = inv_x_lds(g, sizeof(c2<TC>), N > 0);
     allow_lds(k_inv_x<TC, TS, MODE, N>, lds);
     const int nt = g.tiles * p.nz, grid = x_grid(nt, max_blocks);
     if constexpr (MODE == INV_ADD && sizeof(TC) == 4) {  // the refinement's correction

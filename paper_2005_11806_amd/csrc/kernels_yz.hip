@@ -32,17 +32,16 @@ __global__ void __launch_bounds__(256) k_z2d(ZArgs z, c2<T>* __restrict__ spec, 
     const int SP = z.mx;  // elements per plane when ny = 1
     c2<T>* col = spec + (size_t)k0 * SP + m;
     const double lam = z.lamx[m] + z.lamy[0];
-    if constexpr (INV) {
-        chunk_substitute<T, KC>(z, k0, nl, lam, col, SP);
-    } else {
-        c2<T> v[KC];
+    c2<T> v[KC];
 #pragma unroll
-        for (int i = 0; i < KC; ++i) v[i] = i < nl ? col[(size_t)i * SP] : c2<T>{(T)0, (T)0};
-        chunk_eliminate<T, KC>(z, k0, lam, v, 1);
+    for (int i = 0; i < KC; ++i) v[i] = i < nl ? col[(size_t)i * SP] : c2<T>{(T)0, (T)0};
+    if constexpr (INV)
+        chunk_substitute<T, KC>(z, k0, nl, lam, v);
+    else
+        chunk_eliminate<T, KC>(z, k0, lam, v);
 #pragma unroll
-        for (int i = 0; i < KC; ++i)
-            if (i < nl) col[(size_t)i * SP] = v[i];
-    }
+    for (int i = 0; i < KC; ++i)
+        if (i < nl) col[(size_t)i * SP] = v[i];
 }
 
 template <typename T, bool INV>

@@ -54,13 +54,9 @@ inline size_t yz_lds(int ny, int kc, size_t csz) {
     return (lines + ny) * csz;
 }
 
-// LDS layout of the tile's lines: padded for the compile-time lengths (all
-// multiples of 8), plain for the runtime FFT
-template <int N>
-using YzLayout = std::conditional_t<(N > 0), Pad8, NoPad>;
-
 struct ZArgs {
     int nz, mx, ny;
+    FastDiv by_mx, by_ny;  // division by mx and ny
     int kc;          // rows per chunk = planes per y tile (4, 8 or 16)
     int nc;          // chunks per column, ceil(nz / kc)
     double nxny_lz;  // nx * ny * lz
@@ -126,17 +122,13 @@ __device__ __forceinline__ T chunk_row0_pivot(T cc0, T ab1) {
     return (T)1 / ((T)1 - cc0 * ab1);
 }
 
-// Local elimination of one system's chunk (rows col[i * stride], i < KC, in
-// LDS), in registers: forward sweep, and the backward sweep that reduces row
-// 0; rows 1..KC-1 keep their forward-swept right-hand sides.
+// Local elimination of one system's chunk in registers: forward sweep, and the
+// backward sweep that reduces row 0; rows 1..KC-1 keep their forward-swept
+// right-hand sides.
 template <typename T, int KC>
-__device__ __forceinline__ void chunk_eliminate(const ZArgs& z, int k0, double lam, c2<T>* col,
-                                                int stride) {
+__device__ __forceinline__ void chunk_eliminate(const ZArgs& z, int k0, double lam, c2<T>* d) {
     using C = c2<T>;
-    C d[KC];
     T aa[KC], cc[KC];
-#pragma unroll
-    for (int i = 0; i < KC; ++i) d[i] = col[i * stride];
     C dp{(T)0, (T)0};
     T ap = (T)0, cp = (T)0;
 #pragma unroll
@@ -159,22 +151,17 @@ __device__ __forceinline__ void chunk_eliminate(const ZArgs& z, int k0, double l
         const T r0 = chunk_row0_pivot<T>(cc[0], ab);
         d[0] = C{(d[0].x - cc[0] * db.x) * r0, (d[0].y - cc[0] * db.y) * r0};
     }
-#pragma unroll
-    for (int i = 0; i < KC; ++i) col[i * stride] = d[i];
 }
 
-// Back substitution of one system's chunk: rows 0 and KC-1 hold x_first and
-// x_last, rows 1..KC-2 the forward-swept d_i; x_i = d_i - aa_i x_first -
-// cc_i x_{i+1}, from i = KC-2 down. Rows i >= nl are padding (x = 0).
+// Back substitution of one system's chunk in registers: rows 0 and KC-1 hold
+// x_first and x_last, rows 1..KC-2 the forward-swept d_i; x_i = d_i - aa_i
+// x_first - cc_i x_{i+1}, from i = KC-2 down. Rows i >= nl are padding (x = 0).
 template <typename T, int KC>
 __device__ __forceinline__ void chunk_substitute(const ZArgs& z, int k0, int nl, double lam,
-                                                 c2<T>* col, int stride) {
+                                                 c2<T>* d) {
     using C = c2<T>;
     if constexpr (KC >= 3) {
-        C d[KC];
         T aa[KC], cc[KC];
-#pragma unroll
-        for (int i = 0; i < KC; ++i) d[i] = i < nl ? col[i * stride] : C{(T)0, (T)0};
         T ap = (T)0, cp = (T)0;
 #pragma unroll
         for (int i = 0; i < KC - 1; ++i) {
@@ -190,57 +177,234 @@ __device__ __forceinline__ void chunk_substitute(const ZArgs& z, int k0, int nl,
                         : C{(T)0, (T)0};
             d[i] = xn;
         }
-#pragma unroll
-        for (int i = 1; i < KC - 1; ++i)
-            if (i < nl) col[i * stride] = d[i];
     }
 }
 
-// FFT of the tile's lines: in place for a compile-time length N, else the
-// runtime routine with the second buffer; returns the buffer with the result.
-template <typename T, int N, int KC, int DIR>
-__device__ __forceinline__ c2<T>* yz_fft(c2<T>* buf, int ny, int nlines, const Radices& rad,
-                                         const c2<T>* tw) {
-    if constexpr (N > 0) {
-        fft_inplace<N, 0, DIR, 1, KC, YzLayout<N>>(buf, tw);
-        return buf;
-    } else {
-        return lds_fft<DIR>(buf, buf + KC * ny, ny, nlines, ny, rad, tw, ny);
+// Planes and base of y tile b = c mx + m (chunk c, wavenumber m).
+template <typename T>
+struct YzTile {
+    int m, k0, nl;  // wavenumber, first plane, planes
+    size_t SP;      // elements per plane
+    c2<T>* base;    // row 0
+    __device__ __forceinline__ YzTile(const ZArgs& z, int ny, int kc, c2<T>* spec, int b) {
+        const int c = fdiv(b, z.by_mx);
+        m = b - c * z.mx;
+        k0 = c * kc;
+        nl = min(kc, z.nz - k0);
+        SP = (size_t)z.mx * ny;
+        base = spec + (size_t)k0 * SP + (size_t)m * ny;
     }
-}
+};
 
-// Stages the tile's lines (planes [k0, k0 + nl) of wavenumber m; rows past
-// nl read as 0) and the twiddles into LDS.
+// Forward y tile b, compile-time ny = N: the FFT along y of the tile's KC
+// planes and the local elimination of its N systems. The first stage takes its
+// butterflies straight from global memory and the elimination stores its rows
+// straight to it (a thread owns system n, so the lanes of a wave store 64
+// consecutive elements of a plane): between them the tile passes through LDS
+// once per further stage, in place. Against the whole tile staged in LDS first
+// and stored from it last: 59 instead of 91 LDS instructions and 402 instead of
+// 553 vector instructions per wave; 84.5 -> 82.5 us at 256x256x512 FP64 (541 MB,
+// 6.6 TB/s: memory bounds it), 13.4 -> 10.9 at 128^3 (kc 16), where latency does.
 template <typename T, int N, int KC>
-__device__ __forceinline__ void yz_load(const ZArgs& z, const c2<T>* __restrict__ base, size_t SP,
-                                        int nl, const c2<T>* __restrict__ tw_g, c2<T>* buf,
-                                        c2<T>* tw) {
+__device__ __forceinline__ void yz_fwd_tile_ct(const ZArgs& z, c2<T>* __restrict__ spec,
+                                               const c2<T>* __restrict__ tw_g, int b,
+                                               unsigned char* smem) {
     using C = c2<T>;
-    using P = YzLayout<N>;
-    const int ny = N ? N : z.ny;
+    using P = Pad8;
+    constexpr RadixList RL = radix_list(N);
+    constexpr int R = RL.r[0], NB = N / R, TOTAL = KC * NB, IT = (TOTAL + 255) / 256;
+    constexpr int TWP = (N + 255) / 256;
+    C* buf = reinterpret_cast<C*>(smem);
+    C* tw = buf + KC * N + KC * N / 8;  // exp(-2 pi i t / N), t < N
+    const YzTile<T> t0(z, N, KC, spec, b);
+    {
+        C v[IT][R], twr[TWP];
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            const int t = (int)threadIdx.x + it * 256;
+            const int line = t / NB, j = t - line * NB;
+            if (TOTAL % 256 == 0 || t < TOTAL) {
+                // within a chunk (at most 16 planes) offsets fit 32 bits
+                const unsigned o = (unsigned)(line < t0.nl ? line : 0) * (unsigned)t0.SP + (unsigned)j;
+#pragma unroll
+                for (int r = 0; r < R; ++r) v[it][r] = at_off(t0.base, o + r * NB);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < TWP; ++i) {
+            const int e = (int)threadIdx.x + i * 256;
+            twr[i] = tw_g[e < N ? e : 0];
+        }
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            const int t = (int)threadIdx.x + it * 256;
+            const int line = t / NB, j = t - line * NB;
+            if (TOTAL % 256 == 0 || t < TOTAL) {
+                if (line >= t0.nl) {  // planes past the last read as 0
+#pragma unroll
+                    for (int r = 0; r < R; ++r) v[it][r] = C{(T)0, (T)0};
+                }
+                bfly_ct<R, -1>(v[it]);
+                stockham_store_ct<R, 1, P, N % 8 == 0>(buf, j, v[it], line * N);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < TWP; ++i) {
+            const int e = (int)threadIdx.x + i * 256;
+            if (e < N) tw[e] = twr[i];
+        }
+    }
+    __syncthreads();
+    fft_inplace<N, 1, RL.count, -1, KC, P>(buf, tw);
+    for (int n = threadIdx.x; n < N; n += 256) {
+        C d[KC];
+        const C* col = buf + P::at(n);
+#pragma unroll
+        for (int i = 0; i < KC; ++i) d[i] = col[i * P::at(N)];
+        // the (0,0) pair is solved apart
+        if (t0.m != 0 || n != 0) chunk_eliminate<T, KC>(z, t0.k0, z.lamx[t0.m] + z.lamy[n], d);
+#pragma unroll
+        for (int i = 0; i < KC; ++i)
+            if (i < t0.nl) at_off(t0.base + (size_t)i * t0.SP, (unsigned)n) = d[i];
+    }
+}
+
+// Inverse y tile b, compile-time ny = N: x_first and x_last of every system
+// sit in rows 0 and KC-1 (written by the interface pass), the interior rows
+// hold the forward-swept d_i; back substitution in registers straight from
+// global memory, then the inverse FFT along y, whose last stage stores its
+// outputs to it.
+template <typename T, int N, int KC>
+__device__ __forceinline__ void yz_inv_tile_ct(const ZArgs& z, c2<T>* __restrict__ spec,
+                                               const c2<T>* __restrict__ tw_g, int b,
+                                               unsigned char* smem) {
+    using C = c2<T>;
+    using P = Pad8;
+    constexpr RadixList RL = radix_list(N);
+    constexpr int LAST = RL.count - 1, R = RL.r[LAST], NB = N / R;
+    constexpr int TWP = (N + 255) / 256;
+    C* buf = reinterpret_cast<C*>(smem);
+    C* tw = buf + KC * N + KC * N / 8;
+    const YzTile<T> t0(z, N, KC, spec, b);
+    C twr[TWP];
+    for (int n = threadIdx.x; n < N; n += 256) {
+        C d[KC];
+#pragma unroll
+        for (int i = 0; i < KC; ++i) {
+            const C v = at_off(t0.base + (i < t0.nl ? i : 0) * t0.SP, (unsigned)n);
+            d[i] = i < t0.nl ? v : C{(T)0, (T)0};
+        }
+        if (n == (int)threadIdx.x) {  // behind the first system's rows
+#pragma unroll
+            for (int i = 0; i < TWP; ++i) {
+                const int e = (int)threadIdx.x + i * 256;
+                twr[i] = tw_g[e < N ? e : 0];
+            }
+        }
+        if (t0.m != 0 || n != 0)
+            chunk_substitute<T, KC>(z, t0.k0, t0.nl, z.lamx[t0.m] + z.lamy[n], d);
+        C* col = buf + P::at(n);
+#pragma unroll
+        for (int i = 0; i < KC; ++i) col[i * P::at(N)] = d[i];
+    }
+    if constexpr (N < 256) {
+        if ((int)threadIdx.x >= N) twr[0] = C{(T)0, (T)0};
+    }
+#pragma unroll
+    for (int i = 0; i < TWP; ++i) {
+        const int e = (int)threadIdx.x + i * 256;
+        if (e < N) tw[e] = twr[i];
+    }
+    __syncthreads();
+    fft_inplace<N, 0, LAST, +1, KC, P>(buf, tw);
+    for (int t = threadIdx.x; t < t0.nl * NB; t += 256) {
+        const int line = t / NB, j = t - line * NB;
+        C v[R];
+        stockham_load_ct<R, +1, NB, NB, 1, P>(buf, j, tw, v, line * N);
+        const unsigned o = (unsigned)line * (unsigned)t0.SP + (unsigned)j;
+#pragma unroll
+        for (int r = 0; r < R; ++r) at_off(t0.base, o + r * NB) = v[r];
+    }
+}
+
+// Stages a runtime-length tile's lines (rows past nl read as 0) and the
+// twiddles into LDS.
+template <typename T, int KC>
+__device__ __forceinline__ void yz_load_rt(const ZArgs& z, const YzTile<T>& t0,
+                                           const c2<T>* __restrict__ tw_g, c2<T>* buf, c2<T>* tw) {
+    using C = c2<T>;
+    const int ny = z.ny, nel = KC * ny;
     // one index space: the KC lines, then the ny twiddles; rows past nl
     // load row 0 and are stored as 0
-    const int nel = KC * ny;
-    constexpr int G = N > 0 ? ((KC + 1) * N + 255) / 256 < 16 ? ((KC + 1) * N + 255) / 256 : 16 : 8;
-    block_copy<G, C>(
+    block_copy<8, C>(
         nel + ny,
         [&](int e) {
-            const int i = e / ny, n = e - i * ny;
-            return e < nel ? base[(size_t)(i < nl ? i : 0) * SP + n] : tw_g[e - nel];
+            const int i = fdiv(e, z.by_ny), n = e - i * ny;
+            return e < nel ? t0.base[(size_t)(i < t0.nl ? i : 0) * t0.SP + n] : tw_g[e - nel];
         },
         [&](int e, C v) {
             if (e < nel)
-                buf[P::at(e)] = e / ny < nl ? v : C{(T)0, (T)0};
+                buf[e] = fdiv(e, z.by_ny) < t0.nl ? v : C{(T)0, (T)0};
             else
                 tw[e - nel] = v;
         });
     __syncthreads();
 }
 
-// Number of buffer elements the tile's KC lines take in their layout.
-template <int N, int KC>
-__device__ __forceinline__ int yz_span(int ny) {
-    return N ? KC * N + KC * N / 8 : KC * ny;
+template <typename T>
+__device__ __forceinline__ void yz_store_rt(const ZArgs& z, const YzTile<T>& t0, const c2<T>* d) {
+    for (int e = threadIdx.x; e < t0.nl * z.ny; e += 256) {
+        const int i = fdiv(e, z.by_ny);
+        t0.base[(size_t)i * t0.SP + (e - i * z.ny)] = d[e];
+    }
+}
+
+// The tiles for a runtime ny: lines and FFT in two plain LDS buffers.
+template <typename T, int KC>
+__device__ __forceinline__ void yz_fwd_tile_rt(const ZArgs& z, const Radices& rad,
+                                               c2<T>* __restrict__ spec, const c2<T>* __restrict__ tw_g,
+                                               int b, unsigned char* smem) {
+    using C = c2<T>;
+    const int ny = z.ny;
+    C* buf = reinterpret_cast<C*>(smem);
+    C* tw = buf + 2 * KC * ny;  // exp(-2 pi i t / ny), t < ny
+    const YzTile<T> t0(z, ny, KC, spec, b);
+    yz_load_rt<T, KC>(z, t0, tw_g, buf, tw);
+    C* r = lds_fft<-1>(buf, buf + KC * ny, ny, KC, ny, rad, tw, ny);
+    for (int n = threadIdx.x; n < ny; n += 256) {
+        if (t0.m == 0 && n == 0) continue;  // the (0,0) pair is solved apart
+        C d[KC];
+#pragma unroll
+        for (int i = 0; i < KC; ++i) d[i] = r[i * ny + n];
+        chunk_eliminate<T, KC>(z, t0.k0, z.lamx[t0.m] + z.lamy[n], d);
+#pragma unroll
+        for (int i = 0; i < KC; ++i) r[i * ny + n] = d[i];
+    }
+    __syncthreads();
+    yz_store_rt(z, t0, r);
+}
+
+template <typename T, int KC>
+__device__ __forceinline__ void yz_inv_tile_rt(const ZArgs& z, const Radices& rad,
+                                               c2<T>* __restrict__ spec, const c2<T>* __restrict__ tw_g,
+                                               int b, unsigned char* smem) {
+    using C = c2<T>;
+    const int ny = z.ny;
+    C* buf = reinterpret_cast<C*>(smem);
+    C* tw = buf + 2 * KC * ny;
+    const YzTile<T> t0(z, ny, KC, spec, b);
+    yz_load_rt<T, KC>(z, t0, tw_g, buf, tw);
+    for (int n = threadIdx.x; n < ny; n += 256) {
+        if (t0.m == 0 && n == 0) continue;
+        C d[KC];
+#pragma unroll
+        for (int i = 0; i < KC; ++i) d[i] = buf[i * ny + n];
+        chunk_substitute<T, KC>(z, t0.k0, t0.nl, z.lamx[t0.m] + z.lamy[n], d);
+#pragma unroll
+        for (int i = 1; i < KC - 1; ++i) buf[i * ny + n] = d[i];
+    }
+    __syncthreads();
+    yz_store_rt(z, t0, lds_fft<+1>(buf, buf + KC * ny, ny, t0.nl, ny, rad, tw, ny));
 }
 
 // Forward y tile b = c mx + m (chunk c, wavenumber m): FFT along y of planes
@@ -250,57 +414,22 @@ template <typename T, int N, int KC>
 __device__ __forceinline__ void yz_fwd_tile(const ZArgs& z, const Radices& rad,
                                             c2<T>* __restrict__ spec, const c2<T>* __restrict__ tw_g,
                                             int b, unsigned char* smem) {
-    using C = c2<T>;
-    using P = YzLayout<N>;
-    const int ny = N ? N : z.ny;
-    C* buf = reinterpret_cast<C*>(smem);
-    C* tw = buf + (N ? yz_span<N, KC>(ny) : 2 * KC * ny);  // exp(-2 pi i t / ny), t < ny
-    const int c = b / z.mx, m = b - c * z.mx;
-    const int k0 = c * KC;
-    const int nl = min(KC, z.nz - k0);
-    const size_t SP = (size_t)z.mx * ny;
-    C* base = spec + (size_t)k0 * SP + (size_t)m * ny;
-    yz_load<T, N, KC>(z, base, SP, nl, tw_g, buf, tw);
-    C* d = yz_fft<T, N, KC, -1>(buf, ny, KC, rad, tw);
-    for (int n = threadIdx.x; n < ny; n += 256) {
-        if (m == 0 && n == 0) continue;  // the (0,0) pair is solved apart
-        chunk_eliminate<T, KC>(z, k0, z.lamx[m] + z.lamy[n], d + P::at(n), P::at(ny));
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < nl * ny; e += 256) {
-        const int i = e / ny, n = e - i * ny;
-        base[(size_t)i * SP + n] = d[P::at(e)];
-    }
+    if constexpr (N > 0)
+        yz_fwd_tile_ct<T, N, KC>(z, spec, tw_g, b, smem);
+    else
+        yz_fwd_tile_rt<T, KC>(z, rad, spec, tw_g, b, smem);
 }
 
-// Inverse y tile b = c mx + m: x_first and x_last of every system sit in rows
-// 0 and KC-1 (written by the interface pass), the interior rows hold the
-// forward-swept d_i; back substitution, then the inverse FFT along y.
+// Inverse y tile b = c mx + m: back substitution of the chunk's rows, then the
+// inverse FFT along y.
 template <typename T, int N, int KC>
 __device__ __forceinline__ void yz_inv_tile(const ZArgs& z, const Radices& rad,
                                             c2<T>* __restrict__ spec, const c2<T>* __restrict__ tw_g,
                                             int b, unsigned char* smem) {
-    using C = c2<T>;
-    using P = YzLayout<N>;
-    const int ny = N ? N : z.ny;
-    C* buf = reinterpret_cast<C*>(smem);
-    C* tw = buf + (N ? yz_span<N, KC>(ny) : 2 * KC * ny);
-    const int c = b / z.mx, m = b - c * z.mx;
-    const int k0 = c * KC;
-    const int nl = min(KC, z.nz - k0);
-    const size_t SP = (size_t)z.mx * ny;
-    C* base = spec + (size_t)k0 * SP + (size_t)m * ny;
-    yz_load<T, N, KC>(z, base, SP, nl, tw_g, buf, tw);
-    for (int n = threadIdx.x; n < ny; n += 256) {
-        if (m == 0 && n == 0) continue;
-        chunk_substitute<T, KC>(z, k0, nl, z.lamx[m] + z.lamy[n], buf + P::at(n), P::at(ny));
-    }
-    __syncthreads();
-    C* r = yz_fft<T, N, KC, +1>(buf, ny, nl, rad, tw);
-    for (int e = threadIdx.x; e < nl * ny; e += 256) {
-        const int i = e / ny, n = e - i * ny;
-        base[(size_t)i * SP + n] = r[P::at(e)];
-    }
+    if constexpr (N > 0)
+        yz_inv_tile_ct<T, N, KC>(z, spec, tw_g, b, smem);
+    else
+        yz_inv_tile_rt<T, KC>(z, rad, spec, tw_g, b, smem);
 }
 
 // Calls f with the compile-time chunk rows matching kc (4, 8 or 16).
@@ -633,6 +762,8 @@ inline ZArgs make_zargs(const Plan& p, double* mean_out) {
     z.nz = p.nz;
     z.mx = p.mx;
     z.ny = p.ny;
+    z.by_mx = fast_div(p.mx);
+    z.by_ny = fast_div(p.ny);
     z.kc = p.lp.kc;
     z.nc = (p.nz + p.lp.kc - 1) / p.lp.kc;
     z.lz = p.grid.lz;
