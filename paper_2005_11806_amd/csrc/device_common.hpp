@@ -505,6 +505,51 @@ __device__ __forceinline__ T ld_stream(const T* p) {
 // (vmcnt(0); expcnt and lgkmcnt left at their maxima).
 __device__ __forceinline__ void lds_dma_wait() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
+// (value, index) pair that comes first: smaller value, then smaller index
+__device__ __forceinline__ void argmin_merge(double& v, int& i, double v2, int i2) {
+    if (v2 < v || (v2 == v && i2 < i)) {
+        v = v2;
+        i = i2;
+    }
+}
+
+// Block-wide (256 threads) argmin_merge of one pair per thread; the result is on
+// thread 0. sv, si: 4 entries.
+__device__ __forceinline__ void block_argmin(double& v, int& i, double* sv, int* si) {
+    for (int o = 32; o > 0; o >>= 1) argmin_merge(v, i, __shfl_down(v, o, 64), __shfl_down(i, o, 64));
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    if (lane == 0) {
+        sv[w] = v;
+        si[w] = i;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0)
+        for (int k = 1; k < 4; ++k) argmin_merge(v, i, sv[k], si[k]);
+}
+
+// Minimum and its first index over the pairs x2[c0, c1), this thread's share of
+// a block of 256: 16-byte loads, eight in flight, visited in increasing index
+// order so that a strict '<' keeps the first minimum.
+__device__ __forceinline__ void min_share(const double2* x2, size_t c0, size_t c1, double& best, int& bi) {
+    constexpr int U = 8;
+    size_t c = c0 + threadIdx.x;
+    for (; c + (U - 1) * 256 < c1; c += U * 256) {
+        double2 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = ld_stream(x2 + c + u * 256);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (v[u].x < best) { best = v[u].x; bi = (int)(2 * (c + u * 256)); }
+            if (v[u].y < best) { best = v[u].y; bi = (int)(2 * (c + u * 256) + 1); }
+        }
+    }
+    for (; c < c1; c += 256) {
+        const double2 v = ld_stream(x2 + c);
+        if (v.x < best) { best = v.x; bi = (int)(2 * c); }
+        if (v.y < best) { best = v.y; bi = (int)(2 * c + 1); }
+    }
+}
+
 // Block-wide sum of one double per thread (blockDim.x <= 1024, multiple of 64).
 __device__ inline double block_sum(double v, double* sh) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);

@@ -15,31 +15,8 @@ namespace {
 constexpr int RB = 256;      // threads per reduction block
 constexpr int RMAXB = 2048;  // partial blocks of a reduction
 
-// (value, index) pair that comes first: smaller value, then smaller index
-__device__ __forceinline__ void argmin_merge(double& v, int& i, double v2, int i2) {
-    if (v2 < v || (v2 == v && i2 < i)) {
-        v = v2;
-        i = i2;
-    }
-}
-
-// Block-wide argmin_merge of one pair per thread; the result is on thread 0.
-__device__ __forceinline__ void block_argmin(double& v, int& i, double* sv, int* si) {
-    for (int o = 32; o > 0; o >>= 1) argmin_merge(v, i, __shfl_down(v, o, 64), __shfl_down(i, o, 64));
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (lane == 0) {
-        sv[w] = v;
-        si[w] = i;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0)
-        for (int k = 1; k < RB / 64; ++k) argmin_merge(v, i, sv[k], si[k]);
-}
-
 // Per-block minimum of a contiguous share of x[0, n) and the first index
-// where it occurs: pairs (16-byte loads), eight per thread in flight, each
-// thread visiting its pairs in increasing index order so that a strict '<'
-// keeps its first minimum. A second launch merges the blocks' pairs (a
+// where it occurs. A second launch merges the blocks' pairs (a
 // device-scope fence per block, to merge in the last block instead, writes
 // back its L2 and costs more than the launch).
 __global__ void __launch_bounds__(RB) k_min_partial(const double* __restrict__ x, size_t n,
@@ -48,28 +25,10 @@ __global__ void __launch_bounds__(RB) k_min_partial(const double* __restrict__ x
     __shared__ int si[RB / 64];
     double best = __builtin_inf();
     int bi = 0x7fffffff;
-    constexpr int U = 8;
-    const double2* x2 = reinterpret_cast<const double2*>(x);
     const size_t n2 = n / 2;
     const size_t chunk = (n2 + gridDim.x - 1) / gridDim.x;
     const size_t c0 = (size_t)blockIdx.x * chunk;
-    const size_t c1 = c0 + chunk < n2 ? c0 + chunk : n2;
-    size_t c = c0 + threadIdx.x;
-    for (; c + (U - 1) * RB < c1; c += U * RB) {
-        double2 v[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) v[u] = ld_stream(x2 + c + u * RB);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (v[u].x < best) { best = v[u].x; bi = (int)(2 * (c + u * RB)); }
-            if (v[u].y < best) { best = v[u].y; bi = (int)(2 * (c + u * RB) + 1); }
-        }
-    }
-    for (; c < c1; c += RB) {
-        const double2 v = ld_stream(x2 + c);
-        if (v.x < best) { best = v.x; bi = (int)(2 * c); }
-        if (v.y < best) { best = v.y; bi = (int)(2 * c + 1); }
-    }
+    min_share(reinterpret_cast<const double2*>(x), c0, c0 + chunk < n2 ? c0 + chunk : n2, best, bi);
     if ((n & 1) && blockIdx.x == 0 && threadIdx.x == 0 && x[n - 1] < best) {
         best = x[n - 1];
         bi = (int)(n - 1);

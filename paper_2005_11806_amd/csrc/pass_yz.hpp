@@ -676,7 +676,7 @@ __host__ __device__ inline int ifc_qmax(int R) {
 
 // Interface tile b: tile 0 is the (0,0) column; tile b >= 1 solves the
 // interface systems of pairs [(b-1) P, b P), P = IFC_THREADS / L. Needs
-// blockDim.x == IFC_THREADS and QM == ifc_qmax(2 nc) (QM = 0: chosen here).
+// blockDim.x == IFC_THREADS and QM >= ifc_qmax(2 nc) (QM = 0: chosen here).
 template <typename T, int QM = 0>
 __device__ __forceinline__ void ifc_tile(const ZArgs& z, c2<T>* __restrict__ spec, int b,
                                          unsigned char* smem) {
