@@ -80,7 +80,7 @@ static size_t kind_lds(const Plan& p, int kind, bool fp32) {
             return fwd_x_lds(make_xgeom(p), cs, kind == K_RES ? FWD_RESID : p.opts.method == PSV_SPLIT_RHO0 ? FWD_METHOD1 : FWD_CONST,
                              bx_compiled(p.nx / 2));
         case K_INV: case K_INVADD: return inv_x_lds(make_xgeom(p, true), cs, bx_compiled(p.nx / 2));
-        case K_Y: case K_YI: return yz_lds(p.ny, p.lp.kc, cs);
+        case K_Y: case K_YI: return yz_lds(p.ny, p.lp.kc, cs, yz_batch_compiled(p.ny));
         case K_Z: case K_Z2: return ifc_lds(p);
         default: return 0;
     }

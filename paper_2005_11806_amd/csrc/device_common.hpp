@@ -244,18 +244,18 @@ __device__ __forceinline__ void bfly_ct(C* v) {
 }
 
 // Butterfly j of a radix-R Stockham stage (NS = product of the earlier
-// radices, NB = N / R) of the line starting at element off: load with
+// radices, NB = N / R) of the line at in: load with
 // twiddles and transform into v, then store.
 template <int R, int DIR, int NS, int NB, int TSTEP, typename P = NoPad, typename C>
 __device__ __forceinline__ void stockham_load_ct(const C* __restrict__ in, int j,
-                                                 const C* __restrict__ tw, C* v, int off = 0) {
+                                                 const C* __restrict__ tw, C* v) {
     if constexpr (P::linear(NB)) {
-        const int b = P::at(off + j);
+        const int b = P::at(j);
 #pragma unroll
         for (int r = 0; r < R; ++r) v[r] = in[b + r * P::step(NB)];
     } else {
 #pragma unroll
-        for (int r = 0; r < R; ++r) v[r] = in[P::at(off + j + r * NB)];
+        for (int r = 0; r < R; ++r) v[r] = in[P::at(j + r * NB)];
     }
     const int k = j % NS;
     if (NS > 1) {
@@ -269,24 +269,21 @@ __device__ __forceinline__ void stockham_load_ct(const C* __restrict__ in, int j
     bfly_ct<R, DIR>(v);
 }
 
-// A8: off is a multiple of 8 (lines of a length divisible by 8), so in an
-// early stage (NS dividing 8) the outputs of a butterfly are constant offsets
-// apart.
-template <int R, int NS, typename P = NoPad, bool A8 = false, typename C>
-__device__ __forceinline__ void stockham_store_ct(C* __restrict__ out, int j, const C* v,
-                                                  int off = 0) {
-    const int base = off + (j / NS) * NS * R + j % NS;
+// The outputs of a butterfly in an early stage (NS divides 8, NS R is a
+// multiple of 8) are constant offsets apart in either layout: the first lies
+// at a multiple of 8 plus j mod NS, so no other crosses a group of 8 by it.
+template <int R, int NS, typename P = NoPad, typename C>
+__device__ __forceinline__ void stockham_store_ct(C* __restrict__ out, int j, const C* v) {
+    const int base = (j / NS) * NS * R + j % NS;
     if constexpr (P::linear(NS)) {
         const int b = P::at(base);
 #pragma unroll
         for (int r = 0; r < R; ++r) out[b + r * P::step(NS)] = v[r];
-    } else if constexpr (A8 && 8 % NS == 0 && (NS * R) % 8 == 0) {
-        // base mod 8 is below NS, so no output crosses a group of 8 by its
-        // own offset: at(base + r NS) = at(base) + at(r NS)
+    } else if constexpr (8 % NS == 0 && (NS * R) % 8 == 0) {
         const int b = P::at(base);
 #pragma unroll
         for (int r = 0; r < R; ++r) out[b + P::at(r * NS)] = v[r];
-    } else if constexpr (A8 && NS == 1 && 8 % R == 0) {
+    } else if constexpr (NS == 1 && 8 % R == 0) {
         const int b = P::at(base);
 #pragma unroll
         for (int r = 0; r < R; ++r) out[b + r] = v[r];
@@ -331,7 +328,7 @@ __device__ __forceinline__ void line_stage(const C* src, C* dst, int nlines, int
         const int j = t - line * NB;
         C v[R];
         stockham_load_ct<R, DIR, NS, NB, N / (NS * R), P>(src + line * ls, j, tw, v);
-        stockham_store_ct<R, NS, P, N % 8 == 0>(dst + line * ls, j, v);
+        stockham_store_ct<R, NS, P>(dst + line * ls, j, v);
     }
 }
 
@@ -351,11 +348,11 @@ __device__ __forceinline__ C* line_stages(C* src, C* dst, int nlines, int ls,
 }
 
 // In-place variant, stages S .. END - 1 of radix_list(N), for NL lines of
-// length N stored one after the other in one LDS buffer in layout P: every
-// stage reads all of its butterflies into registers (a thread takes
-// butterflies t, t + 256, ...), waits for the block, then writes. Ends with
-// the block synchronised.
-template <int N, int S, int END, int DIR, int NL, typename P = NoPad, typename C>
+// length N, LS elements apart, in one LDS buffer in layout P: every stage
+// reads all of its butterflies into registers (a thread of NT takes
+// butterflies t, t + NT, ...), waits for the block, then writes. Ends with the
+// block synchronised.
+template <int N, int S, int END, int DIR, int NL, int LS, int NT, typename P, typename C>
 __device__ __forceinline__ void fft_inplace(C* buf, const C* __restrict__ tw) {
     constexpr RadixList RL = radix_list(N);
     if constexpr (S < END) {
@@ -364,27 +361,27 @@ __device__ __forceinline__ void fft_inplace(C* buf, const C* __restrict__ tw) {
         constexpr int NB = N / R;
         constexpr int TSTEP = N / (NS * R);
         constexpr int TOTAL = NL * NB;
-        constexpr int IT = (TOTAL + 255) / 256;
+        constexpr int IT = (TOTAL + NT - 1) / NT;
         C v[IT][R];
 #pragma unroll
         for (int it = 0; it < IT; ++it) {
-            const int t = (int)threadIdx.x + it * 256;
-            if (TOTAL % 256 == 0 || t < TOTAL) {
+            const int t = (int)threadIdx.x + it * NT;
+            if (TOTAL % NT == 0 || t < TOTAL) {
                 const int line = t / NB;
-                stockham_load_ct<R, DIR, NS, NB, TSTEP, P>(buf, t - line * NB, tw, v[it], line * N);
+                stockham_load_ct<R, DIR, NS, NB, TSTEP, P>(buf + line * LS, t - line * NB, tw, v[it]);
             }
         }
         __syncthreads();
 #pragma unroll
         for (int it = 0; it < IT; ++it) {
-            const int t = (int)threadIdx.x + it * 256;
-            if (TOTAL % 256 == 0 || t < TOTAL) {
+            const int t = (int)threadIdx.x + it * NT;
+            if (TOTAL % NT == 0 || t < TOTAL) {
                 const int line = t / NB;
-                stockham_store_ct<R, NS, P, N % 8 == 0>(buf, t - line * NB, v[it], line * N);
+                stockham_store_ct<R, NS, P>(buf + line * LS, t - line * NB, v[it]);
             }
         }
         __syncthreads();
-        fft_inplace<N, S + 1, END, DIR, NL, P>(buf, tw);
+        fft_inplace<N, S + 1, END, DIR, NL, LS, NT, P>(buf, tw);
     }
 }
 

@@ -31,12 +31,15 @@ struct Stencil {
     const double* vol;
 };
 
-// x-line lengths (nx/2) with a compile-time FFT; others use the runtime one
+// x-line lengths (nx/2) with a compile-time FFT; others use the runtime one.
+// The batched kernels hold those up to 128 of the first list.
 #define PSV_X_SIZES(X) X(16) X(24) X(32) X(48) X(64) X(96) X(128) X(192) X(256) X(512)
+#define PSV_X_MORE(X) X(8) X(12) X(18) X(36) X(54) X(72) X(108) X(144) X(162) X(384)
 inline bool x_compiled(int M) {
     switch (M) {
 #define PSV_CASE(n) case n:
         PSV_X_SIZES(PSV_CASE)
+        PSV_X_MORE(PSV_CASE)
 #undef PSV_CASE
         return true;
         default: return false;

@@ -34,10 +34,14 @@
 
 namespace psv {
 
-// y-line lengths with a compile-time FFT (in place in one LDS buffer); other
-// lengths use the runtime FFT, which ping-pongs between two buffers
+// y-line lengths with a compile-time FFT; other lengths use the runtime FFT,
+// which ping-pongs between two buffers and takes 1.5 to 3 times as long
+// (512x384x96: 190 us per pass against 50). The batched kernels hold the first
+// list only.
 #define PSV_YZ_SIZES(X) X(32) X(48) X(64) X(96) X(128) X(192) X(256) X(512)
-inline bool yz_compiled(int ny) {
+#define PSV_YZ_MORE(X) \
+    X(16) X(18) X(24) X(36) X(54) X(72) X(108) X(144) X(162) X(216) X(288) X(324) X(384) X(432) X(768) X(1024)
+inline bool yz_batch_compiled(int ny) {
     switch (ny) {
 #define PSV_CASE(n) case n:
         PSV_YZ_SIZES(PSV_CASE)
@@ -46,11 +50,29 @@ inline bool yz_compiled(int ny) {
         default: return false;
     }
 }
+inline bool yz_compiled(int ny) {
+    switch (ny) {
+#define PSV_CASE(n) case n:
+        PSV_YZ_MORE(PSV_CASE)
+#undef PSV_CASE
+        return true;
+        default: return yz_batch_compiled(ny);
+    }
+}
 
-// LDS of a y tile: kc lines (padded by one element per 8 for a compile-time
-// length; two plain buffers of them for a runtime length) and the twiddles
-inline size_t yz_lds(int ny, int kc, size_t csz) {
-    const size_t lines = yz_compiled(ny) ? (size_t)kc * ny + (size_t)kc * ny / 8 : (size_t)2 * kc * ny;
+// LDS elements from one line to the next in a compile-time tile (Pad8 layout)
+__host__ __device__ constexpr int yz_line_span(int n) { return n + (n + 7) / 8; }
+// Threads of a compile-time y tile: 8 elements each up to 2048; larger tiles, of
+// which one or two fit a CU, take 512 threads (ny = 384, kc 8: 62 + 55 us at
+// 512x384x96 against 72 + 75 with 256), except at kc 16, where the sweeps'
+// registers would leave one block per CU (256x256x512 inverse: 151 us against
+// 92 with 256).
+__host__ __device__ constexpr int yz_threads(int n, int kc) { return n * kc > 2048 && kc <= 8 ? 512 : 256; }
+
+// LDS of a y tile: kc lines (two plain buffers of them for a runtime length)
+// and the twiddles
+inline size_t yz_lds(int ny, int kc, size_t csz, bool ct) {
+    const size_t lines = ct ? (size_t)kc * yz_line_span(ny) : (size_t)2 * kc * ny;
     return (lines + ny) * csz;
 }
 
@@ -205,25 +227,26 @@ struct YzTile {
 // and stored from it last: 59 instead of 91 LDS instructions and 402 instead of
 // 553 vector instructions per wave; 84.5 -> 82.5 us at 256x256x512 FP64 (541 MB,
 // 6.6 TB/s: memory bounds it), 13.4 -> 10.9 at 128^3 (kc 16), where latency does.
-template <typename T, int N, int KC>
+template <typename T, int N, int KC, int NT>
 __device__ __forceinline__ void yz_fwd_tile_ct(const ZArgs& z, c2<T>* __restrict__ spec,
                                                const c2<T>* __restrict__ tw_g, int b,
                                                unsigned char* smem) {
     using C = c2<T>;
     using P = Pad8;
     constexpr RadixList RL = radix_list(N);
-    constexpr int R = RL.r[0], NB = N / R, TOTAL = KC * NB, IT = (TOTAL + 255) / 256;
-    constexpr int TWP = (N + 255) / 256;
+    constexpr int R = RL.r[0], NB = N / R, TOTAL = KC * NB, IT = (TOTAL + NT - 1) / NT;
+    constexpr int TWP = (N + NT - 1) / NT;
     C* buf = reinterpret_cast<C*>(smem);
-    C* tw = buf + KC * N + KC * N / 8;  // exp(-2 pi i t / N), t < N
+    constexpr int LS = yz_line_span(N);
+    C* tw = buf + KC * LS;  // exp(-2 pi i t / N), t < N
     const YzTile<T> t0(z, N, KC, spec, b);
     {
         C v[IT][R], twr[TWP];
 #pragma unroll
         for (int it = 0; it < IT; ++it) {
-            const int t = (int)threadIdx.x + it * 256;
+            const int t = (int)threadIdx.x + it * NT;
             const int line = t / NB, j = t - line * NB;
-            if (TOTAL % 256 == 0 || t < TOTAL) {
+            if (TOTAL % NT == 0 || t < TOTAL) {
                 // within a chunk (at most 16 planes) offsets fit 32 bits
                 const unsigned o = (unsigned)(line < t0.nl ? line : 0) * (unsigned)t0.SP + (unsigned)j;
 #pragma unroll
@@ -232,35 +255,35 @@ __device__ __forceinline__ void yz_fwd_tile_ct(const ZArgs& z, c2<T>* __restrict
         }
 #pragma unroll
         for (int i = 0; i < TWP; ++i) {
-            const int e = (int)threadIdx.x + i * 256;
+            const int e = (int)threadIdx.x + i * NT;
             twr[i] = tw_g[e < N ? e : 0];
         }
 #pragma unroll
         for (int it = 0; it < IT; ++it) {
-            const int t = (int)threadIdx.x + it * 256;
+            const int t = (int)threadIdx.x + it * NT;
             const int line = t / NB, j = t - line * NB;
-            if (TOTAL % 256 == 0 || t < TOTAL) {
+            if (TOTAL % NT == 0 || t < TOTAL) {
                 if (line >= t0.nl) {  // planes past the last read as 0
 #pragma unroll
                     for (int r = 0; r < R; ++r) v[it][r] = C{(T)0, (T)0};
                 }
                 bfly_ct<R, -1>(v[it]);
-                stockham_store_ct<R, 1, P, N % 8 == 0>(buf, j, v[it], line * N);
+                stockham_store_ct<R, 1, P>(buf + line * LS, j, v[it]);
             }
         }
 #pragma unroll
         for (int i = 0; i < TWP; ++i) {
-            const int e = (int)threadIdx.x + i * 256;
+            const int e = (int)threadIdx.x + i * NT;
             if (e < N) tw[e] = twr[i];
         }
     }
     __syncthreads();
-    fft_inplace<N, 1, RL.count, -1, KC, P>(buf, tw);
-    for (int n = threadIdx.x; n < N; n += 256) {
+    fft_inplace<N, 1, RL.count, -1, KC, LS, NT, P>(buf, tw);
+    for (int n = threadIdx.x; n < N; n += NT) {
         C d[KC];
         const C* col = buf + P::at(n);
 #pragma unroll
-        for (int i = 0; i < KC; ++i) d[i] = col[i * P::at(N)];
+        for (int i = 0; i < KC; ++i) d[i] = col[i * LS];
         // the (0,0) pair is solved apart
         if (t0.m != 0 || n != 0) chunk_eliminate<T, KC>(z, t0.k0, z.lamx[t0.m] + z.lamy[n], d);
 #pragma unroll
@@ -274,7 +297,7 @@ __device__ __forceinline__ void yz_fwd_tile_ct(const ZArgs& z, c2<T>* __restrict
 // hold the forward-swept d_i; back substitution in registers straight from
 // global memory, then the inverse FFT along y, whose last stage stores its
 // outputs to it.
-template <typename T, int N, int KC>
+template <typename T, int N, int KC, int NT>
 __device__ __forceinline__ void yz_inv_tile_ct(const ZArgs& z, c2<T>* __restrict__ spec,
                                                const c2<T>* __restrict__ tw_g, int b,
                                                unsigned char* smem) {
@@ -282,12 +305,13 @@ __device__ __forceinline__ void yz_inv_tile_ct(const ZArgs& z, c2<T>* __restrict
     using P = Pad8;
     constexpr RadixList RL = radix_list(N);
     constexpr int LAST = RL.count - 1, R = RL.r[LAST], NB = N / R;
-    constexpr int TWP = (N + 255) / 256;
+    constexpr int TWP = (N + NT - 1) / NT;
     C* buf = reinterpret_cast<C*>(smem);
-    C* tw = buf + KC * N + KC * N / 8;
+    constexpr int LS = yz_line_span(N);
+    C* tw = buf + KC * LS;
     const YzTile<T> t0(z, N, KC, spec, b);
     C twr[TWP];
-    for (int n = threadIdx.x; n < N; n += 256) {
+    for (int n = threadIdx.x; n < N; n += NT) {
         C d[KC];
 #pragma unroll
         for (int i = 0; i < KC; ++i) {
@@ -297,7 +321,7 @@ __device__ __forceinline__ void yz_inv_tile_ct(const ZArgs& z, c2<T>* __restrict
         if (n == (int)threadIdx.x) {  // behind the first system's rows
 #pragma unroll
             for (int i = 0; i < TWP; ++i) {
-                const int e = (int)threadIdx.x + i * 256;
+                const int e = (int)threadIdx.x + i * NT;
                 twr[i] = tw_g[e < N ? e : 0];
             }
         }
@@ -305,22 +329,22 @@ __device__ __forceinline__ void yz_inv_tile_ct(const ZArgs& z, c2<T>* __restrict
             chunk_substitute<T, KC>(z, t0.k0, t0.nl, z.lamx[t0.m] + z.lamy[n], d);
         C* col = buf + P::at(n);
 #pragma unroll
-        for (int i = 0; i < KC; ++i) col[i * P::at(N)] = d[i];
+        for (int i = 0; i < KC; ++i) col[i * LS] = d[i];
     }
-    if constexpr (N < 256) {
+    if constexpr (N < NT) {
         if ((int)threadIdx.x >= N) twr[0] = C{(T)0, (T)0};
     }
 #pragma unroll
     for (int i = 0; i < TWP; ++i) {
-        const int e = (int)threadIdx.x + i * 256;
+        const int e = (int)threadIdx.x + i * NT;
         if (e < N) tw[e] = twr[i];
     }
     __syncthreads();
-    fft_inplace<N, 0, LAST, +1, KC, P>(buf, tw);
-    for (int t = threadIdx.x; t < t0.nl * NB; t += 256) {
+    fft_inplace<N, 0, LAST, +1, KC, LS, NT, P>(buf, tw);
+    for (int t = threadIdx.x; t < t0.nl * NB; t += NT) {
         const int line = t / NB, j = t - line * NB;
         C v[R];
-        stockham_load_ct<R, +1, NB, NB, 1, P>(buf, j, tw, v, line * N);
+        stockham_load_ct<R, +1, NB, NB, 1, P>(buf + line * LS, j, tw, v);
         const unsigned o = (unsigned)line * (unsigned)t0.SP + (unsigned)j;
 #pragma unroll
         for (int r = 0; r < R; ++r) at_off(t0.base, o + r * NB) = v[r];
@@ -409,25 +433,26 @@ __device__ __forceinline__ void yz_inv_tile_rt(const ZArgs& z, const Radices& ra
 
 // Forward y tile b = c mx + m (chunk c, wavenumber m): FFT along y of planes
 // [c KC, c KC + KC) and the local elimination of every system (m, n).
-// N = ny as a compile-time constant, or 0 for the runtime-length FFT.
-template <typename T, int N, int KC>
+// N = ny as a compile-time constant (NT threads), or 0 for the runtime-length
+// FFT (256).
+template <typename T, int N, int KC, int NT = 256>
 __device__ __forceinline__ void yz_fwd_tile(const ZArgs& z, const Radices& rad,
                                             c2<T>* __restrict__ spec, const c2<T>* __restrict__ tw_g,
                                             int b, unsigned char* smem) {
     if constexpr (N > 0)
-        yz_fwd_tile_ct<T, N, KC>(z, spec, tw_g, b, smem);
+        yz_fwd_tile_ct<T, N, KC, NT>(z, spec, tw_g, b, smem);
     else
         yz_fwd_tile_rt<T, KC>(z, rad, spec, tw_g, b, smem);
 }
 
 // Inverse y tile b = c mx + m: back substitution of the chunk's rows, then the
 // inverse FFT along y.
-template <typename T, int N, int KC>
+template <typename T, int N, int KC, int NT = 256>
 __device__ __forceinline__ void yz_inv_tile(const ZArgs& z, const Radices& rad,
                                             c2<T>* __restrict__ spec, const c2<T>* __restrict__ tw_g,
                                             int b, unsigned char* smem) {
     if constexpr (N > 0)
-        yz_inv_tile_ct<T, N, KC>(z, spec, tw_g, b, smem);
+        yz_inv_tile_ct<T, N, KC, NT>(z, spec, tw_g, b, smem);
     else
         yz_inv_tile_rt<T, KC>(z, rad, spec, tw_g, b, smem);
 }

@@ -200,7 +200,7 @@ int builtin_shape(Plan& p) {
     if (kc && !kc_fits(p, kc))
         fail(PSV_ERR_UNSUPPORTED_SIZE, "the y tile of chunk_rows planes exceeds the LDS of a block");
     for (int c : {16, 8, 4})
-        if (!kc && yz_lds(p.ny, c, csz) <= 48 * 1024) kc = c;
+        if (!kc && yz_lds(p.ny, c, csz, yz_compiled(p.ny)) <= 48 * 1024) kc = c;
     if (!kc)
         for (int c : {16, 8, 4})
             if (!kc && kc_fits(p, c)) kc = c;
