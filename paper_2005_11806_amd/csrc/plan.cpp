@@ -176,33 +176,50 @@ void plan_geometry(Plan& p, const psv_grid& g, const psv_opts& o) {
     p.rad_y = make_radices(p.ny);
 }
 
-// Built-in launch shapes of the current device: x lines per block bounded by
-// the LDS a block may take (FP64 worst case, leaving 2 KiB for static shared
-// arrays), the caller's stencil variant, and the chunk rows of the z
-// partition (returned, not yet set): the largest of 16, 8, 4 whose y tile
-// takes at most 48 KiB of LDS (three blocks per CU), else the largest that
-// fits a block at all.
+// Lines per x block: the largest of a few counts that divides ny and gives at
+// most 512 pairs of cells, two per thread of the forward tile, in one step
+// (128^3: 18.1 us at 8 lines against 19.7 at 16 and 21.0 at 4; 192^3 49.7 at 4
+// against 55.9 at 8; 512x384x96 149 at 2, as at 4); a count that would leave
+// the block half empty gives way to the next (288x128x128: 42.0 us at 4 lines
+// against 44.3 at 2). Bounded by the LDS a block may take (FP64 worst case,
+// leaving 2 KiB for static shared arrays).
+static int lines_x(const Plan& p, size_t budget) {
+    const int M = p.nx / 2;
+    int best = 1;
+    for (int lb : {2, 3, 4, 6, 8, 12, 16}) {
+        if (p.ny % lb || x_lds_max(p.nx, lb) > budget) continue;
+        if (lb * M <= 512 || (best * M < 320 && lb * M <= 640)) best = lb;
+    }
+    return best;
+}
+
+// Built-in launch shapes of the current device: x lines per block, the caller's
+// stencil variant, and the chunk rows of the z partition (returned, not yet
+// set): 8 where two of its y tiles fit a CU (256x256x512 z solve: 218 us
+// against 294 at 4 rows, twice the interface systems, and 214 at 16; 128^3 26.5
+// against 29.0 and 27.0; 64^3 14.7, 14.7 and 16.5), else 4 (128x486x96, a
+// runtime length: 134 us against 187 at 8), else the largest that fits.
 int builtin_shape(Plan& p) {
     PSV_HIP(hipGetDevice(&p.device));
     int lds_max = 0;
     PSV_HIP(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, p.device));
-    const size_t budget = (size_t)std::min(lds_max, 64 * 1024) - 2048;
-    p.lp.lbx = 1;
-    while (p.lp.lbx * 2 <= 16 && p.ny % (p.lp.lbx * 2) == 0 && x_lds_max(p.nx, p.lp.lbx * 2) <= budget)
-        p.lp.lbx *= 2;
+    p.lp.lbx = lines_x(p, (size_t)std::min(lds_max, 64 * 1024) - 2048);
     // one line per block may take up to the whole LDS (nx = 1024)
     if (x_lds_max(p.nx, p.lp.lbx) > (size_t)std::min(lds_max, LDS_MAX_BLOCK))
         fail(PSV_ERR_UNSUPPORTED_SIZE, "line length exceeds the LDS budget");
     p.lp.lbx_inv = p.lp.lbx;
+    // FP64 inverse, 8 lines (whole 128-byte lines of bins) where they are two
+    // full steps of the block: 256x256x512 81 us against 89 at 4
+    if (p.opts.precision == PSV_FP64 && p.nx == 256 && p.ny % 8 == 0) p.lp.lbx_inv = 8;
     p.lp.xstage = p.opts.x_stencil == 2 ? 0 : 1;
     const size_t csz = p.opts.precision == PSV_MIXED ? sizeof(float2) : sizeof(double2);
     int kc = p.opts.chunk_rows;
     if (kc && !kc_fits(p, kc))
         fail(PSV_ERR_UNSUPPORTED_SIZE, "the y tile of chunk_rows planes exceeds the LDS of a block");
-    for (int c : {16, 8, 4})
-        if (!kc && yz_lds(p.ny, c, csz, yz_compiled(p.ny)) <= 48 * 1024) kc = c;
+    for (int c : {8, 4})
+        if (!kc && kc_fits(p, c) && 2 * yz_lds(p.ny, c, csz, yz_compiled(p.ny)) <= 160 * 1024) kc = c;
     if (!kc)
-        for (int c : {16, 8, 4})
+        for (int c : {4, 8, 16})
             if (!kc && kc_fits(p, c)) kc = c;
     if (!kc) fail(PSV_ERR_UNSUPPORTED_SIZE, "y lines exceed the LDS of a block");
     return kc;
