@@ -246,7 +246,9 @@ __device__ __forceinline__ void bfly_ct(C* v) {
 // Butterfly j of a radix-R Stockham stage (NS = product of the earlier
 // radices, NB = N / R) of the line at in: load with
 // twiddles and transform into v, then store.
-template <int R, int DIR, int NS, int NB, int TSTEP, typename P = NoPad, typename C>
+// SEP keeps the twiddle products apart from the sums they enter (no fused
+// multiply-add across the two), which is how the runtime transform rounds.
+template <int R, int DIR, int NS, int NB, int TSTEP, bool SEP, typename P = NoPad, typename C>
 __device__ __forceinline__ void stockham_load_ct(const C* __restrict__ in, int j,
                                                  const C* __restrict__ tw, C* v) {
     if constexpr (P::linear(NB)) {
@@ -264,6 +266,7 @@ __device__ __forceinline__ void stockham_load_ct(const C* __restrict__ in, int j
             C w = tw[r * k * TSTEP];
             if (DIR > 0) w.y = -w.y;
             v[r] = cmul(v[r], w);
+            if constexpr (SEP) asm("" : "+v"(v[r].x), "+v"(v[r].y));
         }
     }
     bfly_ct<R, DIR>(v);
@@ -318,7 +321,7 @@ struct AllRadices {
 };
 
 // One stage over nlines lines, src to dst (NT threads); the caller synchronises.
-template <int N, int R, int NS, int DIR, int NT, typename P, typename C>
+template <int N, int R, int NS, int DIR, int NT, bool SEP, typename P, typename C>
 __device__ __forceinline__ void line_stage(const C* src, C* dst, int nlines, int ls,
                                            const C* __restrict__ tw) {
     constexpr int NB = N / R;
@@ -327,23 +330,23 @@ __device__ __forceinline__ void line_stage(const C* src, C* dst, int nlines, int
         const int line = t / NB;
         const int j = t - line * NB;
         C v[R];
-        stockham_load_ct<R, DIR, NS, NB, N / (NS * R), P>(src + line * ls, j, tw, v);
+        stockham_load_ct<R, DIR, NS, NB, N / (NS * R), SEP, P>(src + line * ls, j, tw, v);
         stockham_store_ct<R, NS, P>(dst + line * ls, j, v);
     }
 }
 
 // Stages S .. END - 1 of List, ping-ponging between src and dst with a barrier
 // after each; returns the buffer with the result.
-template <int N, typename List, int S, int END, int NS, int DIR, int NT, typename P, typename C>
+template <int N, typename List, int S, int END, int NS, int DIR, int NT, bool SEP, typename P, typename C>
 __device__ __forceinline__ C* line_stages(C* src, C* dst, int nlines, int ls,
                                           const C* __restrict__ tw) {
     if constexpr (S >= END) {
         return src;
     } else {
         constexpr int R = List::list.r[S];
-        line_stage<N, R, NS, DIR, NT, P>(src, dst, nlines, ls, tw);
+        line_stage<N, R, NS, DIR, NT, SEP, P>(src, dst, nlines, ls, tw);
         __syncthreads();
-        return line_stages<N, List, S + 1, END, NS * R, DIR, NT, P>(dst, src, nlines, ls, tw);
+        return line_stages<N, List, S + 1, END, NS * R, DIR, NT, SEP, P>(dst, src, nlines, ls, tw);
     }
 }
 
@@ -352,7 +355,7 @@ __device__ __forceinline__ C* line_stages(C* src, C* dst, int nlines, int ls,
 // reads all of its butterflies into registers (a thread of NT takes
 // butterflies t, t + NT, ...), waits for the block, then writes. Ends with the
 // block synchronised.
-template <int N, int S, int END, int DIR, int NL, int LS, int NT, typename P, typename C>
+template <int N, int S, int END, int DIR, int NL, int LS, int NT, bool SEP, typename P, typename C>
 __device__ __forceinline__ void fft_inplace(C* buf, const C* __restrict__ tw) {
     constexpr RadixList RL = radix_list(N);
     if constexpr (S < END) {
@@ -368,7 +371,7 @@ __device__ __forceinline__ void fft_inplace(C* buf, const C* __restrict__ tw) {
             const int t = (int)threadIdx.x + it * NT;
             if (TOTAL % NT == 0 || t < TOTAL) {
                 const int line = t / NB;
-                stockham_load_ct<R, DIR, NS, NB, TSTEP, P>(buf + line * LS, t - line * NB, tw, v[it]);
+                stockham_load_ct<R, DIR, NS, NB, TSTEP, SEP, P>(buf + line * LS, t - line * NB, tw, v[it]);
             }
         }
         __syncthreads();
@@ -381,7 +384,7 @@ __device__ __forceinline__ void fft_inplace(C* buf, const C* __restrict__ tw) {
             }
         }
         __syncthreads();
-        fft_inplace<N, S + 1, END, DIR, NL, LS, NT, P>(buf, tw);
+        fft_inplace<N, S + 1, END, DIR, NL, LS, NT, SEP, P>(buf, tw);
     }
 }
 

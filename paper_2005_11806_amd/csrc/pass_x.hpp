@@ -35,6 +35,16 @@ struct Stencil {
 // The batched kernels hold those up to 128 of the first list.
 #define PSV_X_SIZES(X) X(16) X(24) X(32) X(48) X(64) X(96) X(128) X(192) X(256) X(512)
 #define PSV_X_MORE(X) X(8) X(12) X(18) X(36) X(54) X(72) X(108) X(144) X(162) X(384)
+// FP32 transforms of the second list round as the runtime ones do (which
+// a batch takes for them): a refined result keeps 1e-10 of that rounding.
+template <typename T>
+__host__ __device__ constexpr bool x_sep(int M) {
+    if (sizeof(T) == 8) return false;
+#define PSV_CASE(n) if (M == n) return false;
+    PSV_X_SIZES(PSV_CASE)
+#undef PSV_CASE
+    return true;
+}
 inline bool x_compiled(int M) {
     switch (M) {
 #define PSV_CASE(n) case n:
@@ -302,6 +312,7 @@ __device__ __forceinline__ void fwd_x_tile_ct(const XGeom& g, const Stencil& st,
                                               double* red) {
     using C = c2<TC>;
     using P = Pad8;
+    constexpr bool SEP = x_sep<TC>(N);
     constexpr int M = N, nx = 2 * N, H = N / 2;
     const int k = fdiv(b, g.by_tiles);
     const int j0 = (b - k * g.tiles) * g.lb;
@@ -529,9 +540,9 @@ __device__ __forceinline__ void fwd_x_tile_ct(const XGeom& g, const Stencil& st,
     __syncthreads();
     C* Z;
     if constexpr (FIRST2)
-        Z = line_stages<N, AfterRadix2<N>, 0, AfterRadix2<N>::list.count, 2, -1, NT, P>(buf0, buf1, lb, ls, tw);
+        Z = line_stages<N, AfterRadix2<N>, 0, AfterRadix2<N>::list.count, 2, -1, NT, SEP, P>(buf0, buf1, lb, ls, tw);
     else
-        Z = line_stages<N, AllRadices<N>, 0, AllRadices<N>::list.count, 1, -1, NT, P>(buf0, buf1, lb, ls, tw);
+        Z = line_stages<N, AllRadices<N>, 0, AllRadices<N>::list.count, 1, -1, NT, SEP, P>(buf0, buf1, lb, ls, tw);
     // Split the half-length transform into the real-input spectrum:
     //   E_m = (Z_m + conj Z_{M-m}) / 2, O_m = (Z_m - conj Z_{M-m}) / (2i),
     //   X_m = E_m + w_m O_m, X_{M-m} = conj(E_m - w_m O_m), w_m = exp(-2 pi i m / nx),
@@ -769,6 +780,7 @@ __device__ __forceinline__ void inv_x_tile_ct(const XGeom& g, const c2<TC>* __re
                                               unsigned char* smem) {
     using C = c2<TC>;
     using P = Pad8;
+    constexpr bool SEP = x_sep<TC>(N);
     constexpr int M = N, H = N / 2;
     const int k = fdiv(b, g.by_tiles);
     const int j0 = (b - k * g.tiles) * g.lb;
@@ -820,7 +832,7 @@ __device__ __forceinline__ void inv_x_tile_ct(const XGeom& g, const c2<TC>* __re
     __syncthreads();
     using L = AllRadices<N>;
     constexpr int LAST = L::list.count - 1;
-    const C* z = line_stages<N, L, 0, LAST, 1, +1, NT, P>(buf0, buf1, lb, ls, tw);
+    const C* z = line_stages<N, L, 0, LAST, 1, +1, NT, SEP, P>(buf0, buf1, lb, ls, tw);
     constexpr int R = L::list.r[LAST], NB = N / R;
     const double s = (MODE == INV_SCALE) ? scale * vol[k] : scale;
     double2* out2 = reinterpret_cast<double2*>(out) + ((size_t)k * g.ny + j0) * M;
@@ -833,7 +845,7 @@ __device__ __forceinline__ void inv_x_tile_ct(const XGeom& g, const c2<TC>* __re
             for (int r = 0; r < R; ++r) old[r] = at_off(out2, c + r * NB);
         }
         C v[R];
-        stockham_load_ct<R, +1, NB, NB, 1, P>(z + line * ls, j, tw, v);
+        stockham_load_ct<R, +1, NB, NB, 1, SEP, P>(z + line * ls, j, tw, v);
 #pragma unroll
         for (int r = 0; r < R; ++r) inv_store<MODE>(out2, c + r * NB, v[r], s, old[r]);
     }

@@ -198,7 +198,11 @@ static int lines_x(const Plan& p, size_t budget) {
 // set): 8 where two of its y tiles fit a CU (256x256x512 z solve: 218 us
 // against 294 at 4 rows, twice the interface systems, and 214 at 16; 128^3 26.5
 // against 29.0 and 27.0; 64^3 14.7, 14.7 and 16.5), else 4 (128x486x96, a
-// runtime length: 134 us against 187 at 8), else the largest that fits.
+// runtime length: 134 us against 187 at 8), else the largest that fits. FP32
+// spectra: the largest of 16, 8, 4 whose tile takes at most 48 KiB as the
+// batched kernels lay it out. Their z solve hardly depends on the rows
+// (256x256x512: 55 us at 16 rows, 57 at 8; 128^3 17.1 and 16.3), while the
+// rounding of their sweeps, which does, shows at 1e-10 of a refined result.
 int builtin_shape(Plan& p) {
     PSV_HIP(hipGetDevice(&p.device));
     int lds_max = 0;
@@ -216,6 +220,12 @@ int builtin_shape(Plan& p) {
     int kc = p.opts.chunk_rows;
     if (kc && !kc_fits(p, kc))
         fail(PSV_ERR_UNSUPPORTED_SIZE, "the y tile of chunk_rows planes exceeds the LDS of a block");
+    if (p.opts.precision == PSV_MIXED)
+        for (int c : {16, 8, 4})
+            if (!kc && yz_lds(p.ny, c, csz, yz_batch_compiled(p.ny)) <= 48 * 1024) kc = c;
+    if (p.opts.precision == PSV_MIXED)
+        for (int c : {16, 8, 4})
+            if (!kc && kc_fits(p, c)) kc = c;
     for (int c : {8, 4})
         if (!kc && kc_fits(p, c) && 2 * yz_lds(p.ny, c, csz, yz_compiled(p.ny)) <= 160 * 1024) kc = c;
     if (!kc)
