@@ -91,6 +91,17 @@ void check_field(const Plan& P, const double* x, bool positive, const char* name
     if (b & 2) psv::fail(PSV_ERR_INVALID_ARG, std::string(name) + " must be > 0 everywhere");
 }
 
+// Whether the check that gates a solve's later passes joins the solve's forward
+// y pass (Job). That takes a launch of about 5 us out of every sweep, but the
+// pass after the last check then runs for nothing: 2 spectra of traffic, 10 us at
+// 32 MiB, against the two or more sweeps of a solve. Method III at 128^3 (17 MB):
+// 956 us joined, 1017 apart; mixed 256 x 256 x 512 (135 MB): 1103 joined, 1068
+// apart.
+bool folds_check(const Plan& P, bool fp32) {
+    const size_t spec = (size_t)P.mx * P.ny * P.nz * (fp32 ? sizeof(float2) : sizeof(double2));
+    return spec <= (size_t)32 << 20;
+}
+
 // One constant-coefficient solve of the system assembled by `a` (CONST or
 // METHOD1), written to `out`. FP64: five passes (x, y with the z chunk
 // elimination, z interface, y with the back substitution, inverse x).
@@ -120,8 +131,8 @@ CoreResult solve_core(Plan& P, psv::FwdArgs a, double* out, bool want_relres, bo
     // assembly pass; the one the FP32 (0,0) column yields is discarded.
     a.partials = mixed ? P.partials : nullptr;
     launch_fwd_x(P, mixed, a, s);
-    if (mixed) launch_mean_finalize(P, fwd_x_blocks(P), P.scal + S_RHS_MEAN, s);
-    launch_z_solve(P, mixed, P.scal + (mixed ? S_MEAN2 : S_RHS_MEAN), nullptr, s);
+    launch_z_solve(P, mixed, P.scal + (mixed ? S_MEAN2 : S_RHS_MEAN), nullptr, s,
+                   mixed ? job_mean(P, fwd_x_blocks(P), s) : Job());
     launch_inv_x(P, mixed, INV_STORE, out, inv_scale, nullptr, s);
     if (!mixed) {
         if (want_relres) {
@@ -139,7 +150,6 @@ CoreResult solve_core(Plan& P, psv::FwdArgs a, double* out, bool want_relres, bo
     ra.partials = P.partials;
     ra.done = done;
     const int maxr = P.opts.max_refine;
-    launch_refine_reset(P, s);
     res.have_relres = true;
     // One refinement sweep usually converges: the x passes that follow its
     // check (and, without host checks, return at once) run on a capped grid,
@@ -148,13 +158,17 @@ CoreResult solve_core(Plan& P, psv::FwdArgs a, double* out, bool want_relres, bo
     for (int sweep = 0;; ++sweep) {
         ra.max_blocks = sweep >= 2 ? SPARE_BLOCKS : 0;
         launch_fwd_x(P, true, ra, s);
-        launch_refine_check(P, fwd_x_blocks(P), sweep, maxr, P.opts.tol, s);
+        Job check = job_refine(P, fwd_x_blocks(P), sweep, maxr, P.opts.tol, s);
+        if (host_checks || sweep == maxr || !folds_check(P, true)) {
+            launch_job(check, s);
+            check = Job();
+        }
         if (host_checks) {
             sync_read(P, s);
             if (P.host_flags[F_DONE]) break;
         }
         if (sweep == maxr) break;
-        launch_z_solve(P, true, P.scal + S_MEAN2, done, s);
+        launch_z_solve(P, true, P.scal + S_MEAN2, done, s, check);
         launch_inv_x(P, true, INV_ADD, out, inv_scale, done, s, sweep >= 1 ? SPARE_BLOCKS : 0);
     }
     if (host_checks) {
@@ -304,8 +318,6 @@ psv_status psv_solve(psv_plan* plan, const double* f, const double* rho, double 
                 psv::launch_fill(p_out, P.ncell(), 0.0, s);
                 p_prev = p_out;
             }
-        } else {
-            psv::launch_set_scalar(P.scal + psv::S_RHO0, 0.0, s);
         }
         a.mode = method1 ? psv::FWD_METHOD1 : psv::FWD_CONST;
         CoreResult cr;
@@ -315,7 +327,7 @@ psv_status psv_solve(psv_plan* plan, const double* f, const double* rho, double 
             info->refine_steps = total_steps;
             info->relres = cr.have_relres ? P.host_scal[psv::S_RELRES] : NAN;
             info->rhs_mean_removed = P.host_scal[psv::S_RHS_MEAN];
-            info->rho0_used = P.host_scal[psv::S_RHO0];
+            info->rho0_used = method1 ? P.host_scal[psv::S_RHO0] : 0.0;
             const bool mixed = P.opts.precision == PSV_MIXED;
             for (int i = 0; i < PSV_RELRES_HISTORY; ++i)
                 info->relres_sweep[i] = mixed ? P.host_scal[psv::S_HIST + i] : NAN;
@@ -421,8 +433,12 @@ static void residual_loop(Plan& P, bool fp32, psv::FwdArgs a, double eps_scale, 
         for (int b = 0; b < batch; ++b, ++launched) {
             a.pprev = has_p ? p_out : nullptr;
             psv::launch_fwd_x(P, fp32, a, s);
-            psv::launch_m3_check(P, qpart, nb, eps_scale, eps_t, has_p, max_iter, s);
-            psv::launch_z_solve(P, fp32, P.scal + psv::S_MEAN2, done, s);
+            psv::Job check = psv::job_m3(P, qpart, nb, eps_scale, eps_t, has_p, max_iter, s);
+            if (!folds_check(P, fp32)) {
+                psv::launch_job(check, s);
+                check = psv::Job();
+            }
+            psv::launch_z_solve(P, fp32, P.scal + psv::S_MEAN2, done, s, check);
             psv::launch_inv_x(P, fp32, has_p ? psv::INV_ADD : psv::INV_STORE, p_out, inv_scale,
                               done, s);
             has_p = true;

@@ -202,12 +202,40 @@ struct FwdArgs {
     int max_blocks;       // > 0: at most this many blocks (FP32 RESID only)
 };
 void launch_fwd_x(const Plan& p, bool fp32, const FwdArgs& a, hipStream_t s);
+// A single-block job on the partial sums of the forward pass before it, done by
+// one extra block of the forward y pass (jobs.hpp): only later passes need its
+// result, and a launch of its own costs each iteration 2.5 to 5 us.
+//  JOB_MEAN:   scal[S_RHS_MEAN] = sum / total; clears the refinement state
+//  JOB_REFINE: the refinement check of sweep `sweep`
+//  JOB_M3:     the iteration check (the loop control below)
+enum JobKind : int { JOB_NONE = 0, JOB_MEAN, JOB_REFINE, JOB_M3 };
+struct Job {
+    int kind = JOB_NONE;
+    const double* partials = nullptr;
+    int nb = 0;
+    double total = 1.0;   // MEAN: volume; M3: scale of the sum
+    double tol = 0.0;     // REFINE, M3: threshold
+    int sweep = 0;        // REFINE
+    int has_p = 0;        // M3
+    int max_iter = 0;     // REFINE: max_refine; M3: max_iter
+    double* scal = nullptr;
+    int* flags = nullptr;
+};
+// Jobs on p.partials (or partials) of nblocks forward blocks. Arrays too long
+// for one block are reduced on stream s first.
+Job job_mean(const Plan& p, int nblocks, hipStream_t s);
+Job job_refine(const Plan& p, int nblocks, int sweep, int max_refine, double tol, hipStream_t s);
+Job job_m3(const Plan& p, const double* partials, int nblocks, double dt, double eps_t, bool has_p,
+           int max_iter, hipStream_t s);
+void launch_job(const Job& j, hipStream_t s);  // as a launch of its own
 // y passes with the chunk elimination (forward) or back substitution
 // (inverse) of the z solve, the interface pass between them, and the three
 // in order; mean_out receives the volume-weighted mean of the RHS.
-void launch_yz(const Plan& p, bool fp32, bool inverse, const int* done, hipStream_t s);
+void launch_yz(const Plan& p, bool fp32, bool inverse, const int* done, hipStream_t s,
+               const Job& job = Job());
 void launch_interface(const Plan& p, bool fp32, double* mean_out, const int* done, hipStream_t s);
-void launch_z_solve(const Plan& p, bool fp32, double* mean_out, const int* done, hipStream_t s);
+void launch_z_solve(const Plan& p, bool fp32, double* mean_out, const int* done, hipStream_t s,
+                    const Job& job = Job());
 // Chunk rows of the z partition: whether kc fits, and setting it (recomputes
 // the interface factor table, synchronising).
 bool kc_fits(const Plan& p, int kc);
@@ -229,14 +257,11 @@ void launch_harmonic_weight(const Plan& p, const double* rho, hipStream_t s);
 void launch_min_reduce(const Plan& p, const double* x, double* out_scalar, int* argmin_out,
                        hipStream_t s);
 void launch_norm_finalize(const Plan& p, int nblocks, double tol, hipStream_t s);
-// Mixed refinement on the device: reset clears flags[F_DONE], F_STEPS, F_CONV
-// and the relres history; check (skipped once F_DONE is set) turns the
+// Mixed refinement on the device: JOB_MEAN clears flags[F_DONE], F_STEPS, F_CONV
+// and the relres history; check (a launch of its own; skipped once F_DONE is set) turns the
 // residual pass's partials into relres, records it as history entry `sweep`,
 // and sets F_DONE and F_CONV when relres <= tol, F_DONE alone when sweep ==
 // max_refine or relres is not finite, else counts a sweep in F_STEPS.
-void launch_refine_reset(const Plan& p, hipStream_t s);
-void launch_refine_check(const Plan& p, int nblocks, int sweep, int max_refine, double tol,
-                         hipStream_t s);
 void launch_residual(const Plan& p, const double* r, const double* p_sol, const double* mean,
                      hipStream_t s);
 // Blocks of the forward x pass (also the number of per-block partial sums it writes).
@@ -262,8 +287,6 @@ void launch_sum_partials(const Plan& p, const double* partials, int nblocks, dou
 // once max_iter solves were launched, else flags[F_STEPS] counts the solve
 // that follows. Nothing changes once F_DONE is set.
 void launch_m3_reset(const Plan& p, hipStream_t s);
-void launch_m3_check(const Plan& p, const double* partials, int nblocks, double dt, double eps_t,
-                     bool has_p, int max_iter, hipStream_t s);
 void launch_adjoint_faces(const Plan& p, const double* x, const double* f, const double* rho,
                           const double* pprev, const double* rho0, double* grad_f,
                           double* grad_rho, double* grad_p, double* partials, hipStream_t s);
@@ -275,8 +298,6 @@ void launch_scale_vol(const Plan& p, const double* x, double* out, hipStream_t s
 void launch_vmean(const Plan& p, const double* r, double* out_scalar, hipStream_t s,
                   const double* scale = nullptr);
 void launch_fill(double* x, size_t n, double v, hipStream_t s);
-// volume-weighted mean from the forward pass's per-block sums of vol * r
-void launch_mean_finalize(const Plan& p, int nblocks, double* out_scalar, hipStream_t s);
 void launch_scan_inputs(const Plan& p, const double* x, int positive, int* bad, hipStream_t s);
 
 }  // namespace psv

@@ -7,7 +7,7 @@
 #include <algorithm>
 #include <cstdint>
 
-#include "internal.hpp"
+#include "jobs.hpp"
 
 namespace psv {
 namespace {
@@ -156,37 +156,9 @@ __global__ void k_relres_final(double* scal, int* flags, double tol) {
     }
 }
 
-__global__ void k_refine_reset(double* scal, int* flags) {
-    if (threadIdx.x < S_NHIST) scal[S_HIST + threadIdx.x] = __builtin_nan("");
-    if (threadIdx.x == 0) {
-        flags[F_DONE] = 0;
-        flags[F_STEPS] = 0;
-        flags[F_CONV] = 0;
-    }
-}
-
-__global__ void __launch_bounds__(RB) k_refine_check(const double* partials, int nb, int sweep,
-                                                     int max_refine, double tol, double* scal,
-                                                     int* flags) {
+__global__ void __launch_bounds__(RB) k_job(Job j) {
     __shared__ double sh[16];
-    if (flags[F_DONE]) return;  // uniform over the block
-    const double2 ab = thread_share2(partials, nb);
-    const double a = block_sum(ab.x, sh);
-    __syncthreads();
-    const double b = block_sum(ab.y, sh);
-    if (threadIdx.x == 0) {
-        const double rr = b > 0.0 ? sqrt(a / b) : 0.0;
-        scal[S_RELRES] = rr;
-        if (sweep < S_NHIST) scal[S_HIST + sweep] = rr;
-        if (rr <= tol) {
-            flags[F_DONE] = 1;
-            flags[F_CONV] = 1;
-        } else if (sweep >= max_refine || !isfinite(rr)) {
-            flags[F_DONE] = 1;
-        } else {
-            flags[F_STEPS] += 1;
-        }
-    }
+    run_job(j, sh);
 }
 
 __global__ void k_m3_reset(int* flags) {
@@ -195,30 +167,6 @@ __global__ void k_m3_reset(int* flags) {
         flags[F_STEPS] = 0;
         flags[F_CONV] = 0;
     }
-}
-
-__global__ void __launch_bounds__(RB) k_m3_check(const double* partials, int nb, double dt,
-                                                 double eps_t, int has_p, int max_iter,
-                                                 double* scal, int* flags) {
-    __shared__ double sh[16];
-    if (flags[F_DONE]) return;  // uniform over the block
-    const double eps = dt * block_sum(thread_share(partials, nb, 1, 0), sh);
-    if (threadIdx.x != 0) return;
-    if (!has_p) {
-        scal[S_EPS0] = eps;
-    } else {
-        scal[S_EPS] = eps;
-        if (eps <= eps_t) {
-            flags[F_CONV] = 1;
-            flags[F_DONE] = 1;
-            return;
-        }
-        if (flags[F_STEPS] >= max_iter) {
-            flags[F_DONE] = 1;
-            return;
-        }
-    }
-    flags[F_STEPS] += 1;
 }
 
 __global__ void k_set_scalar(double* dst, double v) {
@@ -631,22 +579,69 @@ void launch_harmonic_weight(const Plan& p, const double* rho, hipStream_t s) {
     PSV_HIP(hipGetLastError());
 }
 
-// Long partial arrays (more than 2048 entries per sum) first go through
+// Long partial arrays (more than `most` entries per sum) first go through
 // k_partials_stage1 into the last 2 STAGE1_BLOCKS entries of the plan's
 // partials buffer. The x passes' arrays (one or two entries per tile) never
 // reach them, as the buffer holds at least 2 ny nz + 64 entries; a source
 // that spans them is read by the single block directly. Returns the array
 // the final single-block pass reads; nb becomes its length.
 static const double* stage_partials(const Plan& p, const double* partials, int& nb, int per,
-                                    const int* done, hipStream_t s) {
+                                    const int* done, hipStream_t s, int most = 2048) {
     double* out = p.partials + (p.n_partials - 2 * STAGE1_BLOCKS);
     const uintptr_t a0 = (uintptr_t)partials, a1 = (uintptr_t)(partials + (size_t)per * nb);
     const uintptr_t o0 = (uintptr_t)out, o1 = (uintptr_t)(out + 2 * STAGE1_BLOCKS);
-    if (nb <= 2048 || per > 2 || (a0 < o1 && o0 < a1)) return partials;
+    if (nb <= most || per > 2 || (a0 < o1 && o0 < a1)) return partials;
     hipLaunchKernelGGL(k_partials_stage1, dim3(STAGE1_BLOCKS), dim3(RB), 0, s, partials, nb, per,
                        out, done);
+    PSV_HIP(hipGetLastError());
     nb = STAGE1_BLOCKS;
     return out;
+}
+
+// An extra block of the forward y pass takes about 1.5 us per 2048 doubles it
+// sums, behind the pass's own blocks: up to these lengths it ends before a pass
+// over as many tiles does, longer arrays are cheaper in two stages (4 us).
+constexpr int JOB_MAX_1 = 8192, JOB_MAX_2 = 4096;
+
+Job job_mean(const Plan& p, int nblocks, hipStream_t s) {
+    Job j;
+    j.kind = JOB_MEAN;
+    j.nb = nblocks;
+    j.partials = stage_partials(p, p.partials, j.nb, 1, nullptr, s, JOB_MAX_1);
+    double height = 0.0;
+    for (double h : p.h) height += h;
+    j.total = p.dx * p.dy * height * p.nx * p.ny;
+    j.scal = p.scal;
+    j.flags = p.flags;
+    return j;
+}
+
+Job job_refine(const Plan& p, int nblocks, int sweep, int max_refine, double tol, hipStream_t s) {
+    Job j;
+    j.kind = JOB_REFINE;
+    j.nb = nblocks;
+    j.partials = stage_partials(p, p.partials, j.nb, 2, p.flags + F_DONE, s, JOB_MAX_2);
+    j.tol = tol;
+    j.sweep = sweep;
+    j.max_iter = max_refine;
+    j.scal = p.scal;
+    j.flags = p.flags;
+    return j;
+}
+
+Job job_m3(const Plan& p, const double* partials, int nblocks, double dt, double eps_t, bool has_p,
+           int max_iter, hipStream_t s) {
+    Job j;
+    j.kind = JOB_M3;
+    j.nb = nblocks;
+    j.partials = stage_partials(p, partials, j.nb, 1, p.flags + F_DONE, s, JOB_MAX_1);
+    j.total = dt;
+    j.tol = eps_t;
+    j.has_p = has_p ? 1 : 0;
+    j.max_iter = max_iter;
+    j.scal = p.scal;
+    j.flags = p.flags;
+    return j;
 }
 
 void launch_norm_finalize(const Plan& p, int nblocks, double tol, hipStream_t s) {
@@ -657,16 +652,8 @@ void launch_norm_finalize(const Plan& p, int nblocks, double tol, hipStream_t s)
     PSV_HIP(hipGetLastError());
 }
 
-void launch_refine_reset(const Plan& p, hipStream_t s) {
-    hipLaunchKernelGGL(k_refine_reset, dim3(1), dim3(64), 0, s, p.scal, p.flags);
-    PSV_HIP(hipGetLastError());
-}
-
-void launch_refine_check(const Plan& p, int nblocks, int sweep, int max_refine, double tol,
-                         hipStream_t s) {
-    const double* src = stage_partials(p, p.partials, nblocks, 2, p.flags + F_DONE, s);
-    hipLaunchKernelGGL(k_refine_check, dim3(1), dim3(RB), 0, s, src, nblocks, sweep,
-                       max_refine, tol, p.scal, p.flags);
+void launch_job(const Job& j, hipStream_t s) {
+    hipLaunchKernelGGL(k_job, dim3(1), dim3(RB), 0, s, j);
     PSV_HIP(hipGetLastError());
 }
 
@@ -721,14 +708,6 @@ void launch_m3_reset(const Plan& p, hipStream_t s) {
     PSV_HIP(hipGetLastError());
 }
 
-void launch_m3_check(const Plan& p, const double* partials, int nblocks, double dt, double eps_t,
-                     bool has_p, int max_iter, hipStream_t s) {
-    const double* src = stage_partials(p, partials, nblocks, 1, p.flags + F_DONE, s);
-    hipLaunchKernelGGL(k_m3_check, dim3(1), dim3(RB), 0, s, src, nblocks, dt, eps_t,
-                       has_p ? 1 : 0, max_iter, p.scal, p.flags);
-    PSV_HIP(hipGetLastError());
-}
-
 void launch_sum_partials(const Plan& p, const double* partials, int nblocks, double* out,
                          hipStream_t s) {
     const double* src = stage_partials(p, partials, nblocks, 1, nullptr, s);
@@ -766,15 +745,6 @@ void launch_vmean(const Plan& p, const double* r, double* out_scalar, hipStream_
     const int nb = grid_blocks(p.ncell(), RB);
     hipLaunchKernelGGL(k_vsum, dim3(nb), dim3(RB), 0, s, make_geo(p), r, scale, p.partials);
     hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(RB), 0, s, p.partials, nb, 1, out_scalar);
-    double total = 0.0;
-    for (double h : p.h) total += h;
-    hipLaunchKernelGGL(k_div_scalar, dim3(1), dim3(64), 0, s, out_scalar, p.dx * p.dy * total * p.nx * p.ny);
-    PSV_HIP(hipGetLastError());
-}
-
-void launch_mean_finalize(const Plan& p, int nblocks, double* out_scalar, hipStream_t s) {
-    const double* src = stage_partials(p, p.partials, nblocks, 1, nullptr, s);
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(RB), 0, s, src, nblocks, 1, out_scalar);
     double total = 0.0;
     for (double h : p.h) total += h;
     hipLaunchKernelGGL(k_div_scalar, dim3(1), dim3(64), 0, s, out_scalar, p.dx * p.dy * total * p.nx * p.ny);

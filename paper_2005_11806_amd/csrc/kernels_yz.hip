@@ -48,23 +48,24 @@ void check_precision(const Plan& p, bool fp32) {
 
 }  // namespace
 
-void launch_yz(const Plan& p, bool fp32, bool inverse, const int* done, hipStream_t s) {
+void launch_yz(const Plan& p, bool fp32, bool inverse, const int* done, hipStream_t s, const Job& job) {
     check_precision(p, fp32);
     static const char* names[2][2] = {{"yz_fwd_fp64", "yz_inv_fp64"}, {"yz_fwd_fp32", "yz_inv_fp32"}};
     TraceScope ts(p, names[fp32][inverse], s);
     const ZArgs z = make_zargs(p, nullptr);
     if (fp32)
-        launch_yz32(p, z, inverse, done, s);
+        launch_yz32(p, z, inverse, job, done, s);
     else
-        launch_yz64(p, z, inverse, done, s);
+        launch_yz64(p, z, inverse, job, done, s);
     PSV_HIP(hipGetLastError());
 }
 
-void launch_yz64(const Plan& p, const ZArgs& z, bool inverse, const int* done, hipStream_t s) {
+void launch_yz64(const Plan& p, const ZArgs& z, bool inverse, const Job& job, const int* done,
+                 hipStream_t s) {
     if (inverse)
-        yz_dispatch<double, true>(p, z, (double2*)p.spec, p.t.twy64, done, s);
+        yz_dispatch<double, true>(p, z, (double2*)p.spec, p.t.twy64, job, done, s);
     else
-        yz_dispatch<double, false>(p, z, (double2*)p.spec, p.t.twy64, done, s);
+        yz_dispatch<double, false>(p, z, (double2*)p.spec, p.t.twy64, job, done, s);
 }
 
 void launch_interface(const Plan& p, bool fp32, double* mean_out, const int* done, hipStream_t s) {
@@ -78,8 +79,9 @@ void launch_interface(const Plan& p, bool fp32, double* mean_out, const int* don
     PSV_HIP(hipGetLastError());
 }
 
-void launch_z_solve(const Plan& p, bool fp32, double* mean_out, const int* done, hipStream_t s) {
-    launch_yz(p, fp32, false, done, s);
+void launch_z_solve(const Plan& p, bool fp32, double* mean_out, const int* done, hipStream_t s,
+                    const Job& job) {
+    launch_yz(p, fp32, false, done, s, job);
     launch_interface(p, fp32, mean_out, done, s);
     launch_yz(p, fp32, true, done, s);
 }

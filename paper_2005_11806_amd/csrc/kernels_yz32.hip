@@ -3,11 +3,12 @@
 
 namespace psv {
 
-void launch_yz32(const Plan& p, const ZArgs& z, bool inverse, const int* done, hipStream_t s) {
+void launch_yz32(const Plan& p, const ZArgs& z, bool inverse, const Job& job, const int* done,
+                 hipStream_t s) {
     if (inverse)
-        yz_dispatch<float, true>(p, z, (float2*)p.spec, p.t.twy32, done, s);
+        yz_dispatch<float, true>(p, z, (float2*)p.spec, p.t.twy32, job, done, s);
     else
-        yz_dispatch<float, false>(p, z, (float2*)p.spec, p.t.twy32, done, s);
+        yz_dispatch<float, false>(p, z, (float2*)p.spec, p.t.twy32, job, done, s);
 }
 
 }  // namespace psv

@@ -110,7 +110,10 @@ struct ZRow {
     double a, b, c;
 };
 __device__ __forceinline__ ZRow zrow(const ZArgs& z, int k, double lam) {
-    if (k < z.nz) return ZRow{z.za[k], z.zb[k] + lam, z.zc[k]};
+    // through the constant address space: in a tile k is uniform, and the rows'
+    // coefficients then stay in scalar registers whatever else the kernel does
+    using K = const __attribute__((address_space(4))) double*;
+    if (k < z.nz) return ZRow{((K)z.za)[k], ((K)z.zb)[k] + lam, ((K)z.zc)[k]};
     return ZRow{0.0, 1.0, 0.0};
 }
 

@@ -1,0 +1,52 @@
+"""The check that gates the later passes of a refined or iterated solve, inside
+the forward y pass (spectra up to 32 MiB) and as a launch of its own (larger
+ones): both sides of the line, against the oracle at the paths' tolerances
+(mixed 1e-8 and relres 1e-10; Method III iterates 1e-11 at fixed counts)."""
+import numpy as np
+import pytest
+
+import oracle as O
+from oracle import method3 as M3
+import workloads as W
+from tests.gpu_util import dev, host, oracle_inputs, rel_max_err, say
+
+pytestmark = pytest.mark.gpu
+
+
+def _spec(ny, nz):
+    return W.GridSpec(64, ny, nz, 1.0, 1.1, 1.3, W.tanh_faces(nz, 1.3, 1.5))
+
+
+@pytest.mark.parametrize("nz", [496, 497, 8])
+def test_refined(gpu, nz):
+    spec = _spec(256, nz)  # 33 wavenumbers of 8 bytes: 32 MiB at nz = 496
+    g, f, rho, pp = oracle_inputs(W.two_phase_case("folded", spec, 1, 41, n_spheres=3))
+    (ref,), _ = O.solve(f, g, rho, pp, with_relres=False)
+    plan = gpu.Plan(gpu.Grid.from_spec(spec), precision="mixed")
+    say(f"mixed nz {nz}")
+    f, rho, pp = dev(f), dev(rho), dev(pp)
+    p, info = plan.solve(f, rho=rho, p_prev=pp, info=True)   # the host reads each check
+    assert rel_max_err(host(p), ref) <= 1e-8 and info.relres <= 1e-10
+    first = host(p)
+    p = plan.solve(f, rho=rho, p_prev=pp)                    # only the device does
+    assert rel_max_err(host(p), first) <= 1e-10
+
+
+@pytest.mark.parametrize("nz", [248, 249])
+def test_iterated(gpu, nz):
+    spec = _spec(256, nz)  # of 16 bytes: at 248
+    case = W.method3_case("m3", spec, 1, n_spheres=4)
+    g = O.Grid.from_spec(case.base.grid)
+    rho = O.mixture_density(case.base.phi, case.base.rho_gas, case.base.rho_liq)
+    ref = M3.solve(case.base.faces, case.div_target, rho, case.dt, g, eps_t=0.0, max_iter=3)
+    plan = gpu.Plan(gpu.Grid.from_spec(spec))
+    U, R, T = [dev(np.ascontiguousarray(u)) for u in case.base.faces], dev(rho), dev(case.div_target)
+    say(f"method3 nz {nz}")
+    for k in (1, 3):
+        p, _, info = plan.solve_method3(U, T, R, case.dt, eps_t=0.0, max_iter=k, u_out=True)
+        assert info.iterations == k and not info.converged
+        assert rel_max_err(host(p), ref.p[k - 1]) <= 1e-11
+    between = 0.5 * (ref.eps[1] + ref.eps[2])   # met after the third solve
+    p, _, info = plan.solve_method3(U, T, R, case.dt, eps_t=between, max_iter=9, u_out=True)
+    assert info.converged and info.iterations == 3
+    assert rel_max_err(host(p), ref.p[2]) <= 1e-11
