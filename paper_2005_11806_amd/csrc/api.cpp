@@ -148,7 +148,7 @@ CoreResult solve_core(Plan& P, psv::FwdArgs a, double* out, bool want_relres, bo
     ra.pprev = out;
     ra.mean = P.scal + S_RHS_MEAN;
     ra.partials = P.partials;
-    ra.done = done;
+    ra.done = P.flags + F_DONE;
     const int maxr = P.opts.max_refine;
     res.have_relres = true;
     // One refinement sweep usually converges: the x passes that follow its
@@ -422,7 +422,7 @@ static void residual_loop(Plan& P, bool fp32, psv::FwdArgs a, double eps_scale, 
     constexpr int FIRST_BATCH = 4, MAX_BATCH = 32;
     a.mode = psv::FWD_METHOD3;
     a.partials_abs = qpart;
-    a.done = done;
+    a.done = P.flags + psv::F_DONE;
     psv::launch_m3_reset(P, s);
     int batch = eps_t > 0.0 ? FIRST_BATCH : MAX_BATCH;
     double prev_eps = 0.0;

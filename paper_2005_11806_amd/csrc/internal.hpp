@@ -71,7 +71,10 @@ enum Scalar : int {
     S_NHIST = PSV_RELRES_HISTORY,
     S_NSCAL = 32
 };
-enum Flag : int { F_DONE = 0, F_ARGMIN = 1, F_STEPS = 2, F_CONV = 3, F_NFLAG = 8 };
+// F_DONE gates the passes of a refined or iterated solve. The pass whose launch
+// holds the check that may set it reads F_GATE instead, which the forward x pass
+// after that check sets: no block of a launch reads what another one writes.
+enum Flag : int { F_DONE = 0, F_ARGMIN = 1, F_STEPS = 2, F_CONV = 3, F_GATE = 4, F_NFLAG = 8 };
 
 struct DevTables {
     // twiddles exp(-2 pi i t / n)
@@ -198,7 +201,7 @@ struct FwdArgs {
     const double* mean;   // RESID, METHOD3: device scalar removed from r (or f); METHOD3 may pass null
     double* partials;     // RESID: 2 per block
     double* partials_abs; // METHOD3: sum |f - D(rho_f^-1 G p)| per block
-    const int* done;      // skip when *done != 0 (may be null)
+    int* done;            // flags + F_DONE: set F_GATE and skip when set (may be null)
     int max_blocks;       // > 0: at most this many blocks (FP32 RESID only)
 };
 void launch_fwd_x(const Plan& p, bool fp32, const FwdArgs& a, hipStream_t s);
@@ -257,10 +260,10 @@ void launch_harmonic_weight(const Plan& p, const double* rho, hipStream_t s);
 void launch_min_reduce(const Plan& p, const double* x, double* out_scalar, int* argmin_out,
                        hipStream_t s);
 void launch_norm_finalize(const Plan& p, int nblocks, double tol, hipStream_t s);
-// Mixed refinement on the device: JOB_MEAN clears flags[F_DONE], F_STEPS, F_CONV
-// and the relres history; check (a launch of its own; skipped once F_DONE is set) turns the
-// residual pass's partials into relres, records it as history entry `sweep`,
-// and sets F_DONE and F_CONV when relres <= tol, F_DONE alone when sweep ==
+// Mixed refinement on the device: JOB_MEAN clears flags[F_DONE], F_STEPS, F_CONV,
+// F_GATE and the relres history; the check (a job of the forward y pass or a launch
+// of its own; skipped once F_DONE is set) turns the residual pass's partials into
+// relres, records it as history entry `sweep`, and sets F_DONE and F_CONV when relres <= tol, F_DONE alone when sweep ==
 // max_refine or relres is not finite, else counts a sweep in F_STEPS.
 void launch_residual(const Plan& p, const double* r, const double* p_sol, const double* mean,
                      hipStream_t s);

@@ -57,6 +57,7 @@ __device__ __forceinline__ void run_job(const Job& j, double* sh) {
         if (threadIdx.x != 0) return;
         scal[S_RHS_MEAN] = t / j.total;
         flags[F_DONE] = 0;
+        flags[F_GATE] = 0;
         flags[F_STEPS] = 0;
         flags[F_CONV] = 0;
         return;

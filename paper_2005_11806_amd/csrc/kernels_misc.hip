@@ -163,6 +163,7 @@ __global__ void __launch_bounds__(RB) k_job(Job j) {
 
 __global__ void k_m3_reset(int* flags) {
     if (threadIdx.x == 0) {
+        flags[F_GATE] = 0;
         flags[F_DONE] = 0;
         flags[F_STEPS] = 0;
         flags[F_CONV] = 0;

@@ -81,7 +81,9 @@ void launch_interface(const Plan& p, bool fp32, double* mean_out, const int* don
 
 void launch_z_solve(const Plan& p, bool fp32, double* mean_out, const int* done, hipStream_t s,
                     const Job& job) {
-    launch_yz(p, fp32, false, done, s, job);
+    // see F_GATE
+    const int* gate = done && job.kind != JOB_NONE ? done + (F_GATE - F_DONE) : done;
+    launch_yz(p, fp32, false, gate, s, job);
     launch_interface(p, fp32, mean_out, done, s);
     launch_yz(p, fp32, true, done, s);
 }

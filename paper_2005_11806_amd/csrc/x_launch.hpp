@@ -16,13 +16,20 @@ void launch_inv_x32(const Plan& p, int mode, double* out, double scale_all, cons
 
 namespace {
 
+// Whether the solve is over; F_GATE then closes the y passes with checks, too.
+__device__ __forceinline__ bool fwd_skip(int* done) {
+    if (!done || !*done) return false;
+    if (blockIdx.x == 0 && threadIdx.x == 0) done[F_GATE - F_DONE] = 1;
+    return true;
+}
+
 template <typename TC, typename TS, int MODE, int N, bool STAGE>
 __global__ void __launch_bounds__(256) k_fwd_x(XGeom g, Stencil st, FwdArgs a,
                                                 const c2<TC>* __restrict__ tw_g,
                                                 c2<TS>* __restrict__ spec) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     __shared__ double red[16];
-    if (a.done && *a.done) return;
+    if (fwd_skip(a.done)) return;
     const int b = g.win ? xcd_windows(blockIdx.x, g.win, g.tiles, g.by_win) : xcd_remap(blockIdx.x, gridDim.x);
     fwd_x_tile<TC, TS, MODE, N, STAGE>(g, st, a, tw_g, spec, b, smem_raw, red);
 }
@@ -39,7 +46,7 @@ __global__ void __launch_bounds__(256) k_fwd_x_capped(XGeom g, Stencil st, FwdAr
                                                        c2<TS>* __restrict__ spec) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     __shared__ double red[16];
-    if (a.done && *a.done) return;
+    if (fwd_skip(a.done)) return;
     const int nt = g.tiles * g.nz;
     for (int v = blockIdx.x; v < nt; v += gridDim.x) {
         const int b = g.win ? xcd_windows(v, g.win, g.tiles, g.by_win) : xcd_remap(v, nt);
