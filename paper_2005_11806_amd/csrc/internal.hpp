@@ -239,6 +239,9 @@ void launch_yz(const Plan& p, bool fp32, bool inverse, const int* done, hipStrea
 void launch_interface(const Plan& p, bool fp32, double* mean_out, const int* done, hipStream_t s);
 void launch_z_solve(const Plan& p, bool fp32, double* mean_out, const int* done, hipStream_t s,
                     const Job& job = Job());
+// The three in one launch, for problems whose planes of an x wavenumber fit a block
+bool zf_fits(const Plan& p);
+void launch_zf(const Plan& p, bool fp32, double* mean_out, const int* done, hipStream_t s, const Job& job);
 // Chunk rows of the z partition: whether kc fits, and setting it (recomputes
 // the interface factor table, synchronising).
 bool kc_fits(const Plan& p, int kc);

@@ -83,6 +83,11 @@ void launch_z_solve(const Plan& p, bool fp32, double* mean_out, const int* done,
                     const Job& job) {
     // see F_GATE
     const int* gate = done && job.kind != JOB_NONE ? done + (F_GATE - F_DONE) : done;
+    check_precision(p, fp32);
+    if (zf_fits(p)) {
+        launch_zf(p, fp32, mean_out, gate, s, job);
+        return;
+    }
     launch_yz(p, fp32, false, gate, s, job);
     launch_interface(p, fp32, mean_out, done, s);
     launch_yz(p, fp32, true, done, s);

@@ -117,6 +117,11 @@ __device__ __forceinline__ ZRow zrow(const ZArgs& z, int k, double lam) {
     return ZRow{0.0, 1.0, 0.0};
 }
 
+// Rows k0 + i of the system.
+__device__ __forceinline__ auto zrows(const ZArgs& z, int k0, double lam) {
+    return [&z, k0, lam](int i) { return zrow(z, k0 + i, lam); };
+}
+
 // Forward elimination of chunk row i given the reduced row i-1: row i
 // becomes aa x_first + x_i + cc x_{i+1} = d (for i = 0, aa couples to the
 // previous chunk's last unknown). Returns the pivot reciprocal.
@@ -159,16 +164,16 @@ __device__ __forceinline__ T chunk_row0_pivot(T cc0, T ab1) {
 
 // Local elimination of one system's chunk in registers: forward sweep, and the
 // backward sweep that reduces row 0; rows 1..KC-1 keep their forward-swept
-// right-hand sides.
-template <typename T, int KC>
-__device__ __forceinline__ void chunk_eliminate(const ZArgs& z, int k0, double lam, c2<T>* d) {
+// right-hand sides. row(i) gives the system's row i of the chunk.
+template <typename T, int KC, typename Row>
+__device__ __forceinline__ void chunk_eliminate(Row rows, c2<T>* d) {
     using C = c2<T>;
     T aa[KC], cc[KC];
     C dp{(T)0, (T)0};
     T ap = (T)0, cp = (T)0;
 #pragma unroll
     for (int i = 0; i < KC; ++i) {
-        const ZRow row = zrow(z, k0 + i, lam);
+        const ZRow row = rows(i);
         const double r = chunk_fwd<T>(i, row, ap, cp, aa[i], cc[i]);
         d[i] = chunk_fwd_rhs<T>(i, row, r, d[i], dp);
         dp = d[i];
@@ -191,16 +196,15 @@ __device__ __forceinline__ void chunk_eliminate(const ZArgs& z, int k0, double l
 // Back substitution of one system's chunk in registers: rows 0 and KC-1 hold
 // x_first and x_last, rows 1..KC-2 the forward-swept d_i; x_i = d_i - aa_i
 // x_first - cc_i x_{i+1}, from i = KC-2 down. Rows i >= nl are padding (x = 0).
-template <typename T, int KC>
-__device__ __forceinline__ void chunk_substitute(const ZArgs& z, int k0, int nl, double lam,
-                                                 c2<T>* d) {
+template <typename T, int KC, typename Row>
+__device__ __forceinline__ void chunk_substitute(Row rows, int nl, c2<T>* d) {
     using C = c2<T>;
     if constexpr (KC >= 3) {
         T aa[KC], cc[KC];
         T ap = (T)0, cp = (T)0;
 #pragma unroll
         for (int i = 0; i < KC - 1; ++i) {
-            (void)chunk_fwd<T>(i, zrow(z, k0 + i, lam), ap, cp, aa[i], cc[i]);
+            (void)chunk_fwd<T>(i, rows(i), ap, cp, aa[i], cc[i]);
             ap = aa[i];
             cp = cc[i];
         }
@@ -299,7 +303,7 @@ __device__ __forceinline__ void yz_fwd_tile_ct(const ZArgs& z, c2<T>* __restrict
 #pragma unroll
         for (int i = 0; i < KC; ++i) d[i] = col[i * LS];
         // the (0,0) pair is solved apart
-        if (t0.m != 0 || n != 0) chunk_eliminate<T, KC>(z, t0.k0, z.lamx[t0.m] + z.lamy[n], d);
+        if (t0.m != 0 || n != 0) chunk_eliminate<T, KC>(zrows(z, t0.k0, z.lamx[t0.m] + z.lamy[n]), d);
 #pragma unroll
         for (int i = 0; i < KC; ++i)
             if (i < t0.nl) at_off(t0.base + (size_t)i * t0.SP, (unsigned)n) = d[i];
@@ -341,7 +345,7 @@ __device__ __forceinline__ void yz_inv_tile_ct(const ZArgs& z, c2<T>* __restrict
             }
         }
         if (t0.m != 0 || n != 0)
-            chunk_substitute<T, KC>(z, t0.k0, t0.nl, z.lamx[t0.m] + z.lamy[n], d);
+            chunk_substitute<T, KC>(zrows(z, t0.k0, z.lamx[t0.m] + z.lamy[n]), t0.nl, d);
         C* col = buf + P::at(n);
 #pragma unroll
         for (int i = 0; i < KC; ++i) col[i * LS] = d[i];
@@ -415,7 +419,7 @@ __device__ __forceinline__ void yz_fwd_tile_rt(const ZArgs& z, const Radices& ra
         C d[KC];
 #pragma unroll
         for (int i = 0; i < KC; ++i) d[i] = r[i * ny + n];
-        chunk_eliminate<T, KC>(z, t0.k0, z.lamx[t0.m] + z.lamy[n], d);
+        chunk_eliminate<T, KC>(zrows(z, t0.k0, z.lamx[t0.m] + z.lamy[n]), d);
 #pragma unroll
         for (int i = 0; i < KC; ++i) r[i * ny + n] = d[i];
     }
@@ -438,7 +442,7 @@ __device__ __forceinline__ void yz_inv_tile_rt(const ZArgs& z, const Radices& ra
         C d[KC];
 #pragma unroll
         for (int i = 0; i < KC; ++i) d[i] = buf[i * ny + n];
-        chunk_substitute<T, KC>(z, t0.k0, t0.nl, z.lamx[t0.m] + z.lamy[n], d);
+        chunk_substitute<T, KC>(zrows(z, t0.k0, z.lamx[t0.m] + z.lamy[n]), t0.nl, d);
 #pragma unroll
         for (int i = 1; i < KC - 1; ++i) buf[i * ny + n] = d[i];
     }
@@ -508,10 +512,11 @@ __device__ __forceinline__ double wave_excl_scan(double v) {
 // sum_k h_k x_k / lz.
 inline size_t zero_mode_lds(int nz) { return ((size_t)3 * nz + 1) * sizeof(double); }
 
+// Stages the column (all threads; the caller synchronises).
 template <typename TS>
-__device__ __forceinline__ void zero_mode_tile(const ZArgs& z, c2<TS>* col, size_t stride,
-                                               unsigned char* smem) {
-    double* r = reinterpret_cast<double*>(smem);
+__device__ __forceinline__ void zero_mode_stage(const ZArgs& z, const c2<TS>* col, size_t stride,
+                                                double* smem) {
+    double* r = smem;
     double* hh = r + z.nz;
     double* gg = hh + z.nz;  // [nz + 1]
     for (int k = threadIdx.x; k < z.nz; k += blockDim.x) {
@@ -519,9 +524,15 @@ __device__ __forceinline__ void zero_mode_tile(const ZArgs& z, c2<TS>* col, size
         hh[k] = z.h[k];
     }
     for (int k = threadIdx.x; k <= z.nz; k += blockDim.x) gg[k] = z.g[k];
-    __syncthreads();
-    if (threadIdx.x >= 64) return;
-    const int lane = threadIdx.x;
+}
+
+// Solves from the staged values (one wave); put(k, x) stores x_k.
+template <typename Put>
+__device__ __forceinline__ void zero_mode_solve(const ZArgs& z, const double* smem, Put put) {
+    const double* r = smem;
+    const double* hh = r + z.nz;
+    const double* gg = hh + z.nz;
+    const int lane = threadIdx.x & 63;
     const int C = (z.nz + 63) / 64;
     const int k0 = min(lane * C, z.nz), k1 = min(k0 + C, z.nz);
     double s = 0.0;
@@ -546,14 +557,24 @@ __device__ __forceinline__ void zero_mode_tile(const ZArgs& z, c2<TS>* col, size
         hx += hh[k] * x;
     }
     const double shift = wave_sum(hx) / z.lz;
-    using T = decltype(c2<TS>::x);
     x = x0;
     phi = phi0;
     for (int k = k0; k < k1; ++k) {
         if (k > 0) x += gg[k] * phi;
         phi += hh[k] * (r[k] - mean);
-        col[(size_t)k * stride] = c2<TS>{(T)(x - shift), (T)0};
+        put(k, x - shift);
     }
+}
+
+template <typename TS>
+__device__ __forceinline__ void zero_mode_tile(const ZArgs& z, c2<TS>* col, size_t stride,
+                                               unsigned char* smem) {
+    using T = decltype(c2<TS>::x);
+    double* sm = reinterpret_cast<double*>(smem);
+    zero_mode_stage<TS>(z, col, stride, sm);
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    zero_mode_solve(z, sm, [&](int k, double x) { col[(size_t)k * stride] = c2<TS>{(T)x, (T)0}; });
 }
 
 // plane of interface row r: first (even r) or last (odd r) row of chunk r/2
@@ -613,43 +634,30 @@ __host__ __device__ inline size_t ifc_tab_entries(const IfcShape& h) {
 // theirs by a log2(L)-step scan over the wave (shuffles), and every lane then
 // applies its rows from the value coming in. One load and one store per row.
 // Padding slots (j >= Q, r >= R) are identity maps in both directions; lanes
-// with no system (s = 0, the zero mode, or s >= S) carry identity maps
-// through the shuffles and store nothing.
-template <typename T, int QM>
-__device__ __forceinline__ void ifc_scan(const ZArgs& z, c2<T>* __restrict__ spec, int b) {
+// with no system (not act: the zero mode, or past the last) carry identity maps
+// through the shuffles and store nothing. tw is the lane's entry of the factor
+// table's slot 0, lt loads one; ld(r, rhs) gives the right-hand side of row r where rhs is
+// set, st(r, x) takes its solution.
+template <typename T, int QM, typename Lt, typename Ld, typename St>
+__device__ __forceinline__ void ifc_solve(const ZArgs& z, const IfcShape& h, int lane, int g, bool act,
+                                          const T* tw, Lt lt, Ld ld, St st) {
     using C = c2<T>;
-    const int S = z.mx * z.ny;
-    const IfcShape h = ifc_shape(z.nc, S);
     const int R = h.R, L = h.L, Q = h.Q, spw = h.spw;
-    const int lane = (int)threadIdx.x & 63;
-    const int g = lane / spw;
-    // the wave's first system, and its block of the factor table (the last
-    // tile's waves past S read the last block and discard it)
-    const int sw = __builtin_amdgcn_readfirstlane((b - 1) * (IFC_THREADS / L) +
-                                                  ((int)threadIdx.x >> 6) * spw);
-    const int s = sw + (lane - g * spw);
-    const bool act = s < S && s != 0;
     const int r0 = g * Q;
-    const T* tw = reinterpret_cast<const T*>(z.tab) +
-                  (size_t)min(sw / spw, h.W - 1) * Q * 3 * 64 + lane;
-    // 32-bit element offsets (every index here is below nx ny nz < 2^31)
-    const unsigned us = (unsigned)s, uS = (unsigned)S;
     T al[QM], cm[QM];  // forward -A_r I_r, backward -c'_r (identity 1 on padding)
     C d[QM];           // I_r D_r, then d'_r (0 on padding)
-    // Every slot is loaded unconditionally (slots j >= Q read slot 0; the
-    // right-hand side of a slot without a row reads spectrum element s0 of
-    // plane 0) and masked afterwards, so that all 4 QM loads of a lane are
-    // in flight together; loads under per-row branches would each wait.
-    const unsigned s0 = act ? us : 1u;
+    // Every slot is loaded unconditionally (slots j >= Q read slot 0; ld
+    // reads some element for a slot without a right-hand side) and masked
+    // afterwards, so that all 4 QM loads of a lane are in flight together;
+    // loads under per-row branches would each wait.
 #pragma unroll
     for (int j = 0; j < QM; ++j) {
         const int r = r0 + j;
         const bool row = act && j < Q && r < R;
         const bool rhs = row && ifc_plane(z, r) < z.nz;
         const T* tj = tw + (size_t)(j < Q ? j : 0) * 3 * 64;
-        const unsigned od = rhs ? (unsigned)ifc_plane(z, r) * uS + us : s0;
-        const T A = ld_stream(tj), Cc = ld_stream(tj + 64), I = ld_stream(tj + 128);
-        const C D = spec[od];
+        const T A = lt(tj), Cc = lt(tj + 64), I = lt(tj + 128);
+        const C D = ld(r, rhs);
         al[j] = row ? A : (T)1;
         cm[j] = row ? Cc : (T)1;
         d[j] = rhs ? C{I * D.x, I * D.y} : C{(T)0, (T)0};
@@ -704,8 +712,34 @@ __device__ __forceinline__ void ifc_scan(const ZArgs& z, c2<T>* __restrict__ spe
         x = C{cm[j] * x.x + d[j].x, cm[j] * x.y + d[j].y};
         const int r = r0 + j;
         if (act && j < Q && r < R && ifc_plane(z, r) < z.nz)
-            spec[(unsigned)ifc_plane(z, r) * uS + us] = x;
+            st(r, x);
     }
+}
+
+
+// The interface systems of tile b >= 1 in the spectrum.
+template <typename T, int QM>
+__device__ __forceinline__ void ifc_scan(const ZArgs& z, c2<T>* __restrict__ spec, int b) {
+    using C = c2<T>;
+    const int S = z.mx * z.ny;
+    const IfcShape h = ifc_shape(z.nc, S);
+    const int spw = h.spw;
+    const int lane = (int)threadIdx.x & 63;
+    const int g = lane / spw;
+    // the wave's first system, and its block of the factor table (the last
+    // tile's waves past S read the last block and discard it)
+    const int sw = __builtin_amdgcn_readfirstlane((b - 1) * (IFC_THREADS / h.L) +
+                                                  ((int)threadIdx.x >> 6) * spw);
+    const int s = sw + (lane - g * spw);
+    const bool act = s < S && s != 0;
+    const T* tw = reinterpret_cast<const T*>(z.tab) +
+                  (size_t)min(sw / spw, h.W - 1) * h.Q * 3 * 64 + lane;
+    // 32-bit element offsets (every index here is below nx ny nz < 2^31)
+    const unsigned us = (unsigned)s, uS = (unsigned)S, s0 = act ? us : 1u;
+    ifc_solve<T, QM>(
+        z, h, lane, g, act, tw, [](const T* e) { return ld_stream(e); },
+        [&](int r, bool rhs) { return spec[rhs ? (unsigned)ifc_plane(z, r) * uS + us : s0]; },
+        [&](int r, C x) { spec[(unsigned)ifc_plane(z, r) * uS + us] = x; });
 }
 
 // Register rows per lane for R interface rows: 2, 4, 8 or 16 (nz / kc <= 512).

@@ -64,9 +64,9 @@ __global__ void __launch_bounds__(256) k_z2d(ZArgs z, c2<T>* __restrict__ spec, 
 #pragma unroll
     for (int i = 0; i < KC; ++i) v[i] = i < nl ? col[(size_t)i * SP] : c2<T>{(T)0, (T)0};
     if constexpr (INV)
-        chunk_substitute<T, KC>(z, k0, nl, lam, v);
+        chunk_substitute<T, KC>(zrows(z, k0, lam), nl, v);
     else
-        chunk_eliminate<T, KC>(z, k0, lam, v);
+        chunk_eliminate<T, KC>(zrows(z, k0, lam), v);
 #pragma unroll
     for (int i = 0; i < KC; ++i)
         if (i < nl) col[(size_t)i * SP] = v[i];
