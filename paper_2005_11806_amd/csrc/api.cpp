@@ -73,9 +73,9 @@ void need_aligned(std::initializer_list<const void*> ptrs) {
 
 using psv::Plan;
 
+// The plan's scalars and flags (one block, one copy), synchronising.
 void sync_read(const Plan& P, hipStream_t s) {
-    PSV_HIP(hipMemcpyAsync(P.host_scal, P.scal, psv::S_NSCAL * sizeof(double), hipMemcpyDeviceToHost, s));
-    PSV_HIP(hipMemcpyAsync(P.host_flags, P.flags, psv::F_NFLAG * sizeof(int), hipMemcpyDeviceToHost, s));
+    PSV_HIP(hipMemcpyAsync(P.host_scal, P.scal, psv::SCAL_BYTES, hipMemcpyDeviceToHost, s));
     PSV_HIP(hipStreamSynchronize(s));
 }
 
@@ -388,9 +388,11 @@ psv_status psv_solve_adjoint(psv_plan* plan, const double* w, const double* f, c
     });
 }
 
-static void loop_info(Plan& P, hipStream_t s, bool from_init, psv_m3_info* info) {
+// Results of residual_loop, whose last look at the device read them; synchronises
+// where work was enqueued after the loop (after = true).
+static void loop_info(Plan& P, hipStream_t s, bool from_init, bool after, psv_m3_info* info) {
     if (!info) return;
-    sync_read(P, s);
+    if (after) PSV_HIP(hipStreamSynchronize(s));
     info->iterations = P.host_flags[psv::F_STEPS];
     info->converged = P.host_flags[psv::F_CONV];
     info->eps = P.host_scal[psv::S_EPS];
@@ -415,18 +417,18 @@ static void residual_loop(Plan& P, bool fp32, psv::FwdArgs a, double eps_scale, 
     double* qpart = P.partials + nb;  // sum |q| per block
     const double inv_scale = 2.0 / ((double)P.nx * P.ny);
     const int* done = P.flags + psv::F_DONE;
-    // Iterations launched between two looks at the flag: a few at first, then
-    // as many as the contraction seen between the last two looks predicts to
-    // reach eps_t (plus one), at most MAX_BATCH; with eps_t = 0 the loop runs
-    // to max_iter.
+    // Iterations launched between two looks at the flag (each waits for the
+    // device, about 12 us): a few at first, then as many as the contraction over
+    // the last iterations (at most three, from the device's history of eps)
+    // predicts to reach eps_t, plus one, at most MAX_BATCH; with eps_t = 0 the
+    // loop runs to max_iter.
     constexpr int FIRST_BATCH = 4, MAX_BATCH = 32;
+    const int first = has_p ? 0 : 1;
     a.mode = psv::FWD_METHOD3;
     a.partials_abs = qpart;
     a.done = P.flags + psv::F_DONE;
     psv::launch_m3_reset(P, s);
     int batch = eps_t > 0.0 ? FIRST_BATCH : MAX_BATCH;
-    double prev_eps = 0.0;
-    int prev_steps = -1;
     // max_iter solves and one last residual test need at most max_iter + 1 launches
     for (int launched = 0;;) {
         batch = std::max(1, std::min(batch, max_iter + 1 - launched));
@@ -450,13 +452,16 @@ static void residual_loop(Plan& P, bool fp32, psv::FwdArgs a, double eps_scale, 
         if (launched >= max_iter + 1) psv::fail(PSV_ERR_HIP, "iteration loop control failed");
         const int steps = P.host_flags[psv::F_STEPS];
         batch = eps_t > 0.0 ? FIRST_BATCH : MAX_BATCH;
-        if (eps_t > 0.0 && prev_steps >= 0 && steps > prev_steps && eps > 0.0 && eps < prev_eps) {
-            const double rate = std::pow(eps / prev_eps, 1.0 / (steps - prev_steps));
-            const double need = std::log(eps_t / eps) / std::log(rate);
-            batch = (int)std::min<double>(MAX_BATCH, std::max(1.0, std::ceil(need) + 1.0));
+        // entry i & 7 of the history: eps after i solves, from i = first to steps - 1
+        const int span = std::min(3, steps - 1 - first);
+        if (eps_t > 0.0 && span > 0) {
+            const double from = P.host_scal[psv::S_HIST + ((steps - 1 - span) & 7)];
+            if (eps > 0.0 && eps < from) {
+                const double rate = std::pow(eps / from, 1.0 / span);
+                const double need = std::log(eps_t / eps) / std::log(rate);
+                batch = (int)std::min<double>(MAX_BATCH, std::max(1.0, std::ceil(need) + 1.0));
+            }
         }
-        prev_eps = eps;
-        prev_steps = steps;
     }
 }
 
@@ -497,7 +502,7 @@ psv_status psv_solve_method3(psv_plan* plan, const double* ux, const double* uy,
         a.rho = rho;
         residual_loop(P, fp32, a, dt, eps_t, max_iter, p_init, p_out, s);
         if (want_u) psv::launch_correct_velocity(P, ux, uy, uz, p_out, rho, dt, ux_out, uy_out, uz_out, s);
-        loop_info(P, s, p_init != nullptr, info);
+        loop_info(P, s, p_init != nullptr, want_u, info);
     });
 }
 
@@ -550,7 +555,7 @@ psv_status psv_solve_converged(psv_plan* plan, const double* f, const double* rh
             check_field(P, p_init, false, "p_init", s);
         }
         converged_loop(P, f, nullptr, rho, iteration, eps_t, max_iter, p_init, p_out, s);
-        loop_info(P, s, p_init != nullptr, info);
+        loop_info(P, s, p_init != nullptr, false, info);
     });
 }
 
@@ -584,7 +589,7 @@ psv_status psv_solve_converged_adjoint(psv_plan* plan, const double* w, const do
             psv::launch_adjoint_faces(P, lam, nullptr, rho, p ? p : lam, P.scal + psv::S_UNIT,
                                       grad_f, grad_rho, nullptr, P.partials, s);
         }
-        loop_info(P, s, false, info);
+        loop_info(P, s, false, grad_f || grad_rho, info);
     });
 }
 

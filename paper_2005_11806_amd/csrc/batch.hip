@@ -340,8 +340,7 @@ bool batch_infos(psv_batch& B, hipStream_t s, psv_info* infos) {
     bool ok = true;
     for (int p = 0; p < B.n; ++p) {
         Plan& P = *B.plans[p];
-        PSV_HIP(hipMemcpy(P.host_scal, P.scal, S_NSCAL * sizeof(double), hipMemcpyDeviceToHost));
-        PSV_HIP(hipMemcpy(P.host_flags, P.flags, F_NFLAG * sizeof(int), hipMemcpyDeviceToHost));
+        PSV_HIP(hipMemcpy(P.host_scal, P.scal, SCAL_BYTES, hipMemcpyDeviceToHost));
         infos[p].refine_steps = P.host_flags[F_STEPS];
         infos[p].relres = P.host_scal[S_RELRES];
         infos[p].rhs_mean_removed = P.host_scal[S_RHS_MEAN];

@@ -67,7 +67,8 @@ enum Scalar : int {
     S_UNIT = 10,       // the constant 1 (weight of the implicit adjoint's face products)
     S_RHOMAX = 11,     // max rho (Method II weight)
     S_OMEGA = 12,      // Method II weight: harmonic mean of min rho and max rho
-    S_HIST = 16,       // mixed refinement: relres after the FP32 solve and after each sweep
+    S_HIST = 16,       // mixed refinement: relres after the FP32 solve and after each sweep;
+                       // iterated solves: eps after i solves at entry i & 7
     S_NHIST = PSV_RELRES_HISTORY,
     S_NSCAL = 32
 };
@@ -75,6 +76,9 @@ enum Scalar : int {
 // holds the check that may set it reads F_GATE instead, which the forward x pass
 // after that check sets: no block of a launch reads what another one writes.
 enum Flag : int { F_DONE = 0, F_ARGMIN = 1, F_STEPS = 2, F_CONV = 3, F_GATE = 4, F_NFLAG = 8 };
+// A plan's scalars with its flags behind them, read back in one copy.
+constexpr size_t SCAL_BYTES = S_NSCAL * sizeof(double) + F_NFLAG * sizeof(int);
+static_assert(S_NHIST == 8, "the history's index is masked");
 
 struct DevTables {
     // twiddles exp(-2 pi i t / n)
@@ -156,9 +160,9 @@ struct Plan {
     double* r_ws = nullptr;    // FP64 right-hand side [N]
     double* partials = nullptr;
     int n_partials = 0;
-    double* scal = nullptr;    // [S_NSCAL]
+    double* scal = nullptr;    // [S_NSCAL], then the flags (one block of SCAL_BYTES)
     int* flags = nullptr;      // [F_NFLAG]
-    double* host_scal = nullptr;  // pinned mirror
+    double* host_scal = nullptr;  // pinned mirror of the block
     int* host_flags = nullptr;
     size_t ws_bytes = 0;
     bool own_ws = true;

@@ -64,6 +64,7 @@ __device__ __forceinline__ void run_job(const Job& j, double* sh) {
     }
     if (threadIdx.x != 0) return;
     const double eps = j.total * t;
+    scal[S_HIST + (flags[F_STEPS] & 7)] = eps;  // after F_STEPS solves
     if (!j.has_p) {
         scal[S_EPS0] = eps;
     } else {

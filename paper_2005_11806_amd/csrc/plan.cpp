@@ -292,12 +292,11 @@ void plan_init(Plan& p, const psv_grid& g, const psv_opts& o, bool alloc_ws) {
     // two per forward-x block at any lines-per-block (the autotuner may pick 1)
     p.n_partials = std::max(8192, 2 * p.ny * p.nz + 64);
     PSV_HIP(hipMalloc(&p.partials, p.n_partials * sizeof(double)));
-    PSV_HIP(hipMalloc(&p.scal, S_NSCAL * sizeof(double)));
-    PSV_HIP(hipMalloc(&p.flags, F_NFLAG * sizeof(int)));
-    PSV_HIP(hipMemset(p.scal, 0, S_NSCAL * sizeof(double)));
-    PSV_HIP(hipMemset(p.flags, 0, F_NFLAG * sizeof(int)));
-    PSV_HIP(hipHostMalloc(&p.host_scal, S_NSCAL * sizeof(double)));
-    PSV_HIP(hipHostMalloc(&p.host_flags, F_NFLAG * sizeof(int)));
+    PSV_HIP(hipMalloc(&p.scal, SCAL_BYTES));
+    p.flags = reinterpret_cast<int*>(p.scal + S_NSCAL);
+    PSV_HIP(hipMemset(p.scal, 0, SCAL_BYTES));
+    PSV_HIP(hipHostMalloc(&p.host_scal, SCAL_BYTES));
+    p.host_flags = reinterpret_cast<int*>(p.host_scal + S_NSCAL);
     const size_t nspec = p.nspec(), ncell = p.ncell();
     p.ws_bytes = nspec * sizeof(double2) + 2 * ncell * sizeof(double);
     if (alloc_ws) {
@@ -311,7 +310,7 @@ void plan_init(Plan& p, const psv_grid& g, const psv_opts& o, bool alloc_ws) {
 void plan_free(Plan& p) {
     void* ptrs[] = {p.t.twx64, p.t.twx32, p.t.twy64, p.t.twy32, p.t.lamx, p.t.lamy, p.t.za,
                     p.t.zb, p.t.zc, p.t.inv_h, p.t.inv_g, p.t.h, p.t.g, p.t.vol, p.t.inv_vol,
-                    p.partials, p.scal, p.flags, p.ifc_tab};
+                    p.partials, p.scal, p.ifc_tab};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
     if (p.own_ws) {
@@ -319,7 +318,6 @@ void plan_free(Plan& p) {
         if (p.r_ws) (void)hipFree(p.r_ws);
     }
     if (p.host_scal) (void)hipHostFree(p.host_scal);
-    if (p.host_flags) (void)hipHostFree(p.host_flags);
     p = Plan{};
 }
 
