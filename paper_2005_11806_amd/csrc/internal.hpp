@@ -75,7 +75,16 @@ enum Scalar : int {
 // F_DONE gates the passes of a refined or iterated solve. The pass whose launch
 // holds the check that may set it reads F_GATE instead, which the forward x pass
 // after that check sets: no block of a launch reads what another one writes.
-enum Flag : int { F_DONE = 0, F_ARGMIN = 1, F_STEPS = 2, F_CONV = 3, F_GATE = 4, F_NFLAG = 8 };
+enum Flag : int { F_DONE = 0, F_ARGMIN = 1, F_STEPS = 2, F_CONV = 3, F_GATE = 4, F_LAST = 5, F_REDO = 6, F_NFLAG = 8 };
+// Refinement residuals whose spectrum may be left out. A check tells whether the
+// next residual should meet tol (F_LAST); the next check moves that to F_REDO, for
+// the pass that makes up for the spectrum if it did not.
+enum FwdNorm : int {
+    NORM_NONE = 0,
+    NORM_IF_LAST,  // the norm alone if F_LAST
+    NORM_ALONE,    // the norm alone
+    NORM_REDO      // the whole pass if F_REDO, else nothing
+};
 // A plan's scalars with its flags behind them, read back in one copy.
 constexpr size_t SCAL_BYTES = S_NSCAL * sizeof(double) + F_NFLAG * sizeof(int);
 static_assert(S_NHIST == 8, "the history's index is masked");
@@ -207,6 +216,7 @@ struct FwdArgs {
     double* partials_abs; // METHOD3: sum |f - D(rho_f^-1 G p)| per block
     int* done;            // flags + F_DONE: set F_GATE and skip when set (may be null)
     int max_blocks;       // > 0: at most this many blocks (FP32 RESID only)
+    int norm;             // FwdNorm (FP32 RESID with done only)
 };
 void launch_fwd_x(const Plan& p, bool fp32, const FwdArgs& a, hipStream_t s);
 // A single-block job on the partial sums of the forward pass before it, done by

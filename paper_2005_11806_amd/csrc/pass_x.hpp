@@ -309,7 +309,7 @@ template <typename TC, typename TS, int MODE, int N, bool STAGE, int NT>
 __device__ __forceinline__ void fwd_x_tile_ct(const XGeom& g, const Stencil& st, const FwdArgs& a,
                                               const c2<TC>* __restrict__ tw_g,
                                               c2<TS>* __restrict__ spec, int b, unsigned char* smem,
-                                              double* red) {
+                                              double* red, bool norm_only) {
     using C = c2<TC>;
     using P = Pad8;
     constexpr bool SEP = x_sep<TC>(N);
@@ -537,6 +537,7 @@ __device__ __forceinline__ void fwd_x_tile_ct(const XGeom& g, const Stencil& st,
     auto task_m = [&](int t) { return fdiv(t, g.by_lb); };
     C ws = tw_g[(int)threadIdx.x < ntask ? task_m((int)threadIdx.x) : 0];
     fwd_partials<MODE>(a, st, sum, k, b, red);
+    if (MODE == FWD_RESID && norm_only) return;
     __syncthreads();
     C* Z;
     if constexpr (FIRST2)
@@ -578,7 +579,7 @@ template <typename TC, typename TS, int MODE, bool STAGE>
 __device__ __forceinline__ void fwd_x_tile_rt(const XGeom& g, const Stencil& st, const FwdArgs& a,
                                               const c2<TC>* __restrict__ tw_g,
                                               c2<TS>* __restrict__ spec, int b, unsigned char* smem,
-                                              double* red) {
+                                              double* red, bool norm_only) {
     using C = c2<TC>;
     const int k = fdiv(b, g.by_tiles);
     const int j0 = (b - k * g.tiles) * g.lb;
@@ -717,6 +718,7 @@ __device__ __forceinline__ void fwd_x_tile_rt(const XGeom& g, const Stencil& st,
         }
     }
     fwd_partials<MODE>(a, st, sum, k, b, red);
+    if (MODE == FWD_RESID && norm_only) return;
     __syncthreads();
     C* Z = lds_fft<-1>(buf0, buf1, M, lb, M, g.rad, tw, 2 * M);
     // Split the half-length transform into the real-input spectrum:
@@ -737,15 +739,16 @@ __device__ __forceinline__ void fwd_x_tile_rt(const XGeom& g, const Stencil& st,
 }
 
 // Forward tile b. N = nx/2 as a compile-time constant, or 0 (runtime length).
+// norm_only (RESID): the partial sums alone, without the transform.
 template <typename TC, typename TS, int MODE, int N, bool STAGE = true, int NT = 256>
 __device__ __forceinline__ void fwd_x_tile(const XGeom& g, const Stencil& st, const FwdArgs& a,
                                            const c2<TC>* __restrict__ tw_g,
                                            c2<TS>* __restrict__ spec, int b, unsigned char* smem,
-                                           double* red) {
+                                           double* red, bool norm_only = false) {
     if constexpr (N > 0)
-        fwd_x_tile_ct<TC, TS, MODE, N, STAGE, NT>(g, st, a, tw_g, spec, b, smem, red);
+        fwd_x_tile_ct<TC, TS, MODE, N, STAGE, NT>(g, st, a, tw_g, spec, b, smem, red, norm_only);
     else
-        fwd_x_tile_rt<TC, TS, MODE, STAGE>(g, st, a, tw_g, spec, b, smem, red);
+        fwd_x_tile_rt<TC, TS, MODE, STAGE>(g, st, a, tw_g, spec, b, smem, red, norm_only);
 }
 
 // One result of an inverse tile (pair index c): p = s x, or p = old + s x.

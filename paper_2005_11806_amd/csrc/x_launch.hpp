@@ -23,6 +23,15 @@ __device__ __forceinline__ bool fwd_skip(int* done) {
     return true;
 }
 
+// Whether a refinement residual's pass leaves the spectrum out, and whether it is
+// not needed (FwdNorm)
+__device__ __forceinline__ bool norm_alone(const FwdArgs& a) {
+    return a.norm == NORM_ALONE || (a.norm == NORM_IF_LAST && a.done[F_LAST - F_DONE]);
+}
+__device__ __forceinline__ bool norm_had_spectrum(const FwdArgs& a) {
+    return a.norm == NORM_REDO && !a.done[F_REDO - F_DONE];
+}
+
 template <typename TC, typename TS, int MODE, int N, bool STAGE>
 __global__ void __launch_bounds__(256) k_fwd_x(XGeom g, Stencil st, FwdArgs a,
                                                 const c2<TC>* __restrict__ tw_g,
@@ -30,8 +39,10 @@ __global__ void __launch_bounds__(256) k_fwd_x(XGeom g, Stencil st, FwdArgs a,
     extern __shared__ __align__(16) unsigned char smem_raw[];
     __shared__ double red[16];
     if (fwd_skip(a.done)) return;
+    if (MODE == FWD_RESID && norm_had_spectrum(a)) return;
+    const bool norm_only = MODE == FWD_RESID && norm_alone(a);
     const int b = g.win ? xcd_windows(blockIdx.x, g.win, g.tiles, g.by_win) : xcd_remap(blockIdx.x, gridDim.x);
-    fwd_x_tile<TC, TS, MODE, N, STAGE>(g, st, a, tw_g, spec, b, smem_raw, red);
+    fwd_x_tile<TC, TS, MODE, N, STAGE>(g, st, a, tw_g, spec, b, smem_raw, red, norm_only);
 }
 
 // The same on a capped grid (a multiple of 8 blocks): block v takes tiles v,
@@ -46,11 +57,12 @@ __global__ void __launch_bounds__(256) k_fwd_x_capped(XGeom g, Stencil st, FwdAr
                                                        c2<TS>* __restrict__ spec) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     __shared__ double red[16];
-    if (fwd_skip(a.done)) return;
+    if (fwd_skip(a.done) || norm_had_spectrum(a)) return;
+    const bool norm_only = norm_alone(a);
     const int nt = g.tiles * g.nz;
     for (int v = blockIdx.x; v < nt; v += gridDim.x) {
         const int b = g.win ? xcd_windows(v, g.win, g.tiles, g.by_win) : xcd_remap(v, nt);
-        fwd_x_tile<TC, TS, MODE, N, STAGE>(g, st, a, tw_g, spec, b, smem_raw, red);
+        fwd_x_tile<TC, TS, MODE, N, STAGE>(g, st, a, tw_g, spec, b, smem_raw, red, norm_only);
         if (v + (int)gridDim.x < nt) __syncthreads();  // the next tile reuses the LDS
     }
 }
