@@ -86,7 +86,7 @@ def kernel_bytes(name, nx, ny, nz, kc=None):
         return 8 * n + c * ns
     if name.startswith("fwd_x_method3"):
         return 3 * 8 * n + c * ns
-    if name.startswith("yz_"):
+    if name.startswith(("yz_", "z_solve")):
         return 2 * c * ns
     if name.startswith("z_interface"):
         if kc is None:
@@ -164,6 +164,8 @@ def trace_name(rocprof_name):
         return f"yz_{'inv' if inv == 'true' else 'fwd'}_{prec}"
     if "k_ifc<" in n:
         return f"z_interface_{prec}"
+    if "k_zf<" in n:
+        return f"z_solve_{prec}"
     if "k_min_partial" in n or "k_min_final" in n:
         return "min_rho"
     if "k_residual" in n:
