@@ -21,6 +21,15 @@ template <typename C>
 __device__ __forceinline__ C csub(C a, C b) { return C{a.x - b.x, a.y - b.y}; }
 template <typename C>
 __device__ __forceinline__ C cmul(C a, C b) { return C{a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x}; }
+// SEP: the product's fused multiply-adds written out as those of the runtime
+// transforms are compiled. Left to the compiler, which of the two products is
+// rounded, and whether one is fused with the sums that follow, changes from
+// length to length.
+template <bool SEP, typename C>
+__device__ __forceinline__ C cmul_sep(C a, C b) {
+    if constexpr (SEP) return C{fma(a.x, b.x, -(a.y * b.y)), fma(a.y, b.x, a.x * b.y)};
+    return cmul(a, b);
+}
 template <typename C>
 __device__ __forceinline__ C cconj(C a) { return C{a.x, -a.y}; }
 template <typename C, typename T>
@@ -246,8 +255,6 @@ __device__ __forceinline__ void bfly_ct(C* v) {
 // Butterfly j of a radix-R Stockham stage (NS = product of the earlier
 // radices, NB = N / R) of the line at in: load with
 // twiddles and transform into v, then store.
-// SEP keeps the twiddle products apart from the sums they enter (no fused
-// multiply-add across the two), which is how the runtime transform rounds.
 template <int R, int DIR, int NS, int NB, int TSTEP, bool SEP, typename P = NoPad, typename C>
 __device__ __forceinline__ void stockham_load_ct(const C* __restrict__ in, int j,
                                                  const C* __restrict__ tw, C* v) {
@@ -265,8 +272,7 @@ __device__ __forceinline__ void stockham_load_ct(const C* __restrict__ in, int j
         for (int r = 1; r < R; ++r) {
             C w = tw[r * k * TSTEP];
             if (DIR > 0) w.y = -w.y;
-            v[r] = cmul(v[r], w);
-            if constexpr (SEP) asm("" : "+v"(v[r].x), "+v"(v[r].y));
+            v[r] = cmul_sep<SEP>(v[r], w);
         }
     }
     bfly_ct<R, DIR>(v);

@@ -565,7 +565,7 @@ __device__ __forceinline__ void fwd_x_tile_ct(const XGeom& g, const Stencil& st,
         } else {
             const C e = C{(TC)0.5 * (zm.x + zc.x), (TC)0.5 * (zm.y - zc.y)};
             const C o = C{(TC)0.5 * (zm.y + zc.y), (TC)-0.5 * (zm.x - zc.x)};
-            const C wo = cmul(ws, o);
+            const C wo = cmul_sep<SEP>(o, ws);
             x0 = cadd(e, wo);
             x1 = cconj(csub(e, wo));
         }
@@ -812,7 +812,7 @@ __device__ __forceinline__ void inv_x_tile_ct(const XGeom& g, const c2<TC>* __re
         if (m == 0) xm.y = xc.y = (TC)0;
         const C e = C{(TC)0.5 * (xm.x + xc.x), (TC)0.5 * (xm.y - xc.y)};
         const C d = C{(TC)0.5 * (xm.x - xc.x), (TC)0.5 * (xm.y + xc.y)};
-        const C o = cmul(d, cconj(w));
+        const C o = cmul_sep<SEP>(d, cconj(w));
         C* zl = buf0 + line * ls;
         zl[P::at(m)] = C{e.x - o.y, e.y + o.x};
         zl[P::at(m == 0 ? H : M - m)] = m == 0 ? cconj(xh) : C{e.x + o.y, o.x - e.y};
