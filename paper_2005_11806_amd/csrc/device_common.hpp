@@ -21,13 +21,15 @@ template <typename C>
 __device__ __forceinline__ C csub(C a, C b) { return C{a.x - b.x, a.y - b.y}; }
 template <typename C>
 __device__ __forceinline__ C cmul(C a, C b) { return C{a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x}; }
-// SEP: the product's fused multiply-adds written out as those of the runtime
-// transforms are compiled. Left to the compiler, which of the two products is
-// rounded, and whether one is fused with the sums that follow, changes from
-// length to length.
-template <bool SEP, typename C>
+// The product's fused multiply-adds written out, where SEP is not 0: 1 as those of
+// the runtime transforms are compiled, 2 with the other product of the imaginary
+// part rounded. Left to the compiler, which of the two products is rounded, and
+// whether one is fused with the sums that follow, changes with the length and
+// with what surrounds the transform.
+template <int SEP, typename C>
 __device__ __forceinline__ C cmul_sep(C a, C b) {
-    if constexpr (SEP) return C{fma(a.x, b.x, -(a.y * b.y)), fma(a.y, b.x, a.x * b.y)};
+    if constexpr (SEP == 1) return C{fma(a.x, b.x, -(a.y * b.y)), fma(a.y, b.x, a.x * b.y)};
+    if constexpr (SEP == 2) return C{fma(a.x, b.x, -(a.y * b.y)), fma(a.x, b.y, a.y * b.x)};
     return cmul(a, b);
 }
 template <typename C>
@@ -255,7 +257,7 @@ __device__ __forceinline__ void bfly_ct(C* v) {
 // Butterfly j of a radix-R Stockham stage (NS = product of the earlier
 // radices, NB = N / R) of the line at in: load with
 // twiddles and transform into v, then store.
-template <int R, int DIR, int NS, int NB, int TSTEP, bool SEP, typename P = NoPad, typename C>
+template <int R, int DIR, int NS, int NB, int TSTEP, int SEP, typename P = NoPad, typename C>
 __device__ __forceinline__ void stockham_load_ct(const C* __restrict__ in, int j,
                                                  const C* __restrict__ tw, C* v) {
     if constexpr (P::linear(NB)) {
@@ -327,7 +329,7 @@ struct AllRadices {
 };
 
 // One stage over nlines lines, src to dst (NT threads); the caller synchronises.
-template <int N, int R, int NS, int DIR, int NT, bool SEP, typename P, typename C>
+template <int N, int R, int NS, int DIR, int NT, int SEP, typename P, typename C>
 __device__ __forceinline__ void line_stage(const C* src, C* dst, int nlines, int ls,
                                            const C* __restrict__ tw) {
     constexpr int NB = N / R;
@@ -343,7 +345,7 @@ __device__ __forceinline__ void line_stage(const C* src, C* dst, int nlines, int
 
 // Stages S .. END - 1 of List, ping-ponging between src and dst with a barrier
 // after each; returns the buffer with the result.
-template <int N, typename List, int S, int END, int NS, int DIR, int NT, bool SEP, typename P, typename C>
+template <int N, typename List, int S, int END, int NS, int DIR, int NT, int SEP, typename P, typename C>
 __device__ __forceinline__ C* line_stages(C* src, C* dst, int nlines, int ls,
                                           const C* __restrict__ tw) {
     if constexpr (S >= END) {
@@ -361,7 +363,7 @@ __device__ __forceinline__ C* line_stages(C* src, C* dst, int nlines, int ls,
 // reads all of its butterflies into registers (a thread of NT takes
 // butterflies t, t + NT, ...), waits for the block, then writes. Ends with the
 // block synchronised.
-template <int N, int S, int END, int DIR, int NL, int LS, int NT, bool SEP, typename P, typename C>
+template <int N, int S, int END, int DIR, int NL, int LS, int NT, int SEP, typename P, typename C>
 __device__ __forceinline__ void fft_inplace(C* buf, const C* __restrict__ tw) {
     constexpr RadixList RL = radix_list(N);
     if constexpr (S < END) {

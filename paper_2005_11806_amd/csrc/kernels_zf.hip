@@ -44,7 +44,7 @@ __host__ __device__ inline ZfLayout zf_layout(int nz, int ny, int kc, const IfcS
 
 // One FFT stage over all planes in place; total butterflies at most
 // ZF_ELEMENTS / R.
-template <int N, int S, int END, int DIR, bool SEP, typename C>
+template <int N, int S, int END, int DIR, int SEP, typename C>
 __device__ __forceinline__ void zf_stages(C* buf, int nz, const C* tw) {
     using P = Pad8;
     constexpr RadixList RL = radix_list(N);
@@ -81,7 +81,7 @@ __global__ void __launch_bounds__(ZF_THREADS) k_zf(ZArgs z, c2<T>* __restrict__ 
         run_job(job, reinterpret_cast<double*>(smem_raw));
         return;
     }
-    constexpr bool SEP = N > 1 && yz_sep<T>(N);
+    constexpr int SEP = N > 1 ? yz_sep<T>(N, -1) : 0;
     constexpr int SB = N > 1 ? N : 4;  // systems per plane of the block
     constexpr int NN = N > 1 ? N : 2;  // (for the transform's constants)
     constexpr RadixList RL = radix_list(NN);

@@ -35,15 +35,19 @@ struct Stencil {
 // The batched kernels hold those up to 128 of the first list.
 #define PSV_X_SIZES(X) X(16) X(24) X(32) X(48) X(64) X(96) X(128) X(192) X(256) X(512)
 #define PSV_X_MORE(X) X(8) X(12) X(18) X(36) X(54) X(72) X(108) X(144) X(162) X(384)
-// FP32 transforms of the second list round as the runtime ones do (which
-// a batch takes for them): a refined result keeps 1e-10 of that rounding.
+// How FP32 transforms round their twiddle products (cmul_sep): a refined or
+// iterated result keeps 1e-10 of that rounding. Lengths of the second list take
+// the runtime transform's way (which a batch takes for them), the others what
+// the compiler makes of them but for two whose choice is written out. dir: -1
+// forward, +1 inverse.
 template <typename T>
-__host__ __device__ constexpr bool x_sep(int M) {
-    if (sizeof(T) == 8) return false;
-#define PSV_CASE(n) if (M == n) return false;
+__host__ __device__ constexpr int x_sep(int M, int dir) {
+    if (sizeof(T) == 8) return 0;
+    if (M == 64 || M == 512) return dir < 0 ? 2 : 0;
+#define PSV_CASE(n) if (M == n) return 0;
     PSV_X_SIZES(PSV_CASE)
 #undef PSV_CASE
-    return true;
+    return 1;
 }
 inline bool x_compiled(int M) {
     switch (M) {
@@ -312,7 +316,7 @@ __device__ __forceinline__ void fwd_x_tile_ct(const XGeom& g, const Stencil& st,
                                               double* red, bool norm_only) {
     using C = c2<TC>;
     using P = Pad8;
-    constexpr bool SEP = x_sep<TC>(N);
+    constexpr int SEP = x_sep<TC>(N, -1);
     constexpr int M = N, nx = 2 * N, H = N / 2;
     const int k = fdiv(b, g.by_tiles);
     const int j0 = (b - k * g.tiles) * g.lb;
@@ -565,7 +569,7 @@ __device__ __forceinline__ void fwd_x_tile_ct(const XGeom& g, const Stencil& st,
         } else {
             const C e = C{(TC)0.5 * (zm.x + zc.x), (TC)0.5 * (zm.y - zc.y)};
             const C o = C{(TC)0.5 * (zm.y + zc.y), (TC)-0.5 * (zm.x - zc.x)};
-            const C wo = cmul_sep<SEP>(o, ws);
+            const C wo = cmul_sep<SEP == 1>(o, ws);
             x0 = cadd(e, wo);
             x1 = cconj(csub(e, wo));
         }
@@ -783,7 +787,7 @@ __device__ __forceinline__ void inv_x_tile_ct(const XGeom& g, const c2<TC>* __re
                                               unsigned char* smem) {
     using C = c2<TC>;
     using P = Pad8;
-    constexpr bool SEP = x_sep<TC>(N);
+    constexpr int SEP = x_sep<TC>(N, 1);
     constexpr int M = N, H = N / 2;
     const int k = fdiv(b, g.by_tiles);
     const int j0 = (b - k * g.tiles) * g.lb;

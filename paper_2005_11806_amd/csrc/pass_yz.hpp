@@ -50,15 +50,15 @@ inline bool yz_batch_compiled(int ny) {
         default: return false;
     }
 }
-// FP32 transforms of the second list round as the runtime ones do (which
-// a batch takes for them): a refined result keeps 1e-10 of that rounding.
+// Rounding of the FP32 twiddle products, as x_sep; dir: -1 forward, +1 inverse.
 template <typename T>
-__host__ __device__ constexpr bool yz_sep(int ny) {
-    if (sizeof(T) == 8) return false;
-#define PSV_CASE(n) if (ny == n) return false;
+__host__ __device__ constexpr int yz_sep(int ny, int dir) {
+    if (sizeof(T) == 8) return 0;
+    if (ny == 512) return dir < 0 ? 2 : 0;
+#define PSV_CASE(n) if (ny == n) return 0;
     PSV_YZ_SIZES(PSV_CASE)
 #undef PSV_CASE
-    return true;
+    return 1;
 }
 inline bool yz_compiled(int ny) {
     switch (ny) {
@@ -250,7 +250,7 @@ __device__ __forceinline__ void yz_fwd_tile_ct(const ZArgs& z, c2<T>* __restrict
                                                unsigned char* smem) {
     using C = c2<T>;
     using P = Pad8;
-    constexpr bool SEP = yz_sep<T>(N);
+    constexpr int SEP = yz_sep<T>(N, -1);
     constexpr RadixList RL = radix_list(N);
     constexpr int R = RL.r[0], NB = N / R, TOTAL = KC * NB, IT = (TOTAL + NT - 1) / NT;
     constexpr int TWP = (N + NT - 1) / NT;
@@ -321,7 +321,7 @@ __device__ __forceinline__ void yz_inv_tile_ct(const ZArgs& z, c2<T>* __restrict
                                                unsigned char* smem) {
     using C = c2<T>;
     using P = Pad8;
-    constexpr bool SEP = yz_sep<T>(N);
+    constexpr int SEP = yz_sep<T>(N, 1);
     constexpr RadixList RL = radix_list(N);
     constexpr int LAST = RL.count - 1, R = RL.r[LAST], NB = N / R;
     constexpr int TWP = (N + NT - 1) / NT;
