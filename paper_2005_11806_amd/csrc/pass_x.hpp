@@ -150,7 +150,7 @@ __device__ __forceinline__ double lap_cell(const double* __restrict__ p, int i, 
 struct FwdCtx {
     double rho0, two_r0, mean, sc, omega, idx2, idy2, igt, igb, ih;
     bool const_w, has_p;
-    int up, dn;  // offset of the plane above and below, 0 at a wall
+    int up, dn;  // planes to the operand above and below
 };
 template <int MODE>
 __device__ __forceinline__ FwdCtx fwd_ctx(const XGeom& g, const Stencil& st, const FwdArgs& a, int k) {
@@ -165,12 +165,16 @@ __device__ __forceinline__ FwdCtx fwd_ctx(const XGeom& g, const Stencil& st, con
     x.omega = x.const_w ? *a.rho0 : 0.0;
     x.idx2 = g.inv_dx * g.inv_dx;
     x.idy2 = g.inv_dy * g.inv_dy;
-    // no flux through a wall: the plane itself stands in for the one beyond, so
-    // that the tile has no branches over its z faces (inv_g is 0 there too)
-    x.up = k + 1 < g.nz ? 1 : 0;
-    x.dn = k > 0 ? 1 : 0;
-    x.igt = x.up ? st.inv_g[k + 1] : 0.0;
-    x.igb = x.dn ? st.inv_g[k] : 0.0;
+    // no flux through a wall: the plane on the other side stands in for the one
+    // beyond (nz >= 2) and inv_g is taken as 0, so that the tile has no branches
+    // over its z faces. What is multiplied by that 0 is then the flux of the face
+    // on the other side, finite wherever the result is (the plane itself would
+    // not do: a wall cell of density 0 divides by 0 + 0 there).
+    const bool top = k + 1 == g.nz, bottom = k == 0;
+    x.up = top ? -1 : 1;
+    x.dn = bottom ? -1 : 1;
+    x.igt = top ? 0.0 : st.inv_g[k + 1];
+    x.igb = bottom ? 0.0 : st.inv_g[k];
     x.ih = st.inv_h[k];
     // Method III without a pressure iterate reads p as 0
     x.has_p = MODE != FWD_METHOD3 || a.pprev != nullptr;
@@ -346,7 +350,7 @@ __device__ __forceinline__ void fwd_x_tile_ct(const XGeom& g, const Stencil& st,
     // the tile's first pair; a pair of the tile is an offset c from it
     const size_t base = (size_t)k * plane + (size_t)j0 * M;
     const double2 *ft = fg + base, *pk = pg + base, *rk = rg + base;
-    const size_t upo = (size_t)plane * x.up, dno = (size_t)plane * x.dn;
+    const ptrdiff_t upo = (ptrdiff_t)plane * x.up, dno = (ptrdiff_t)plane * x.dn;
     const double2 *pup = pk + upo, *pdn = pk - dno, *rup = rk + upo, *rdn = rk - dno;
     auto z_operands = [&](FwdPre& q, unsigned c) {
         q.f = at_off(ft, c);
