@@ -32,13 +32,22 @@ void ifc_dispatch(const Plan& p, const ZArgs& z, const int* done, hipStream_t s)
 
 constexpr int TAB_THREADS = 64;
 
-template <typename T>
+template <typename T, int KC>
 __global__ void __launch_bounds__(TAB_THREADS) k_ifc_table(ZArgs z, T* __restrict__ tab) {
-    extern __shared__ __align__(16) unsigned char smem_raw[];
     const int s = blockIdx.x * TAB_THREADS + (int)threadIdx.x;
-    if (s >= z.mx * z.ny) return;
-    c2<double>* scratch = reinterpret_cast<c2<double>*>(smem_raw) + threadIdx.x;
-    ifc_table_pair<T>(z, s, tab, scratch, TAB_THREADS);
+    if (s < z.mx * z.ny) ifc_table_pair<T, KC>(z, s, tab);
+}
+
+template <typename T>
+void ifc_table_launch(const Plan& p, hipStream_t s) {
+    const ZArgs z = make_zargs(p, nullptr);
+    const dim3 grid((p.mx * p.ny + TAB_THREADS - 1) / TAB_THREADS), block(TAB_THREADS);
+    T* tab = reinterpret_cast<T*>(p.ifc_tab);
+    switch (p.lp.kc) {
+        case 4: hipLaunchKernelGGL((k_ifc_table<T, 4>), grid, block, 0, s, z, tab); break;
+        case 8: hipLaunchKernelGGL((k_ifc_table<T, 8>), grid, block, 0, s, z, tab); break;
+        default: hipLaunchKernelGGL((k_ifc_table<T, 16>), grid, block, 0, s, z, tab); break;
+    }
 }
 
 void check_precision(const Plan& p, bool fp32) {
@@ -107,19 +116,10 @@ size_t ifc_table_bytes(const Plan& p, int kc) {
 }
 
 void launch_ifc_table(const Plan& p, hipStream_t s) {
-    const bool fp32 = p.opts.precision == PSV_MIXED;
-    const ZArgs z = make_zargs(p, nullptr);
-    const int nblk = (p.mx * p.ny + TAB_THREADS - 1) / TAB_THREADS;
-    const size_t lds = (size_t)p.lp.kc * TAB_THREADS * sizeof(double2);
-    if (fp32) {
-        allow_lds(k_ifc_table<float>, lds);
-        hipLaunchKernelGGL(k_ifc_table<float>, dim3(nblk), dim3(TAB_THREADS), lds, s, z,
-                           (float*)p.ifc_tab);
-    } else {
-        allow_lds(k_ifc_table<double>, lds);
-        hipLaunchKernelGGL(k_ifc_table<double>, dim3(nblk), dim3(TAB_THREADS), lds, s, z,
-                           (double*)p.ifc_tab);
-    }
+    if (p.opts.precision == PSV_MIXED)
+        ifc_table_launch<float>(p, s);
+    else
+        ifc_table_launch<double>(p, s);
     PSV_HIP(hipGetLastError());
 }
 

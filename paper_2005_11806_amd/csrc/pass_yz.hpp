@@ -773,59 +773,71 @@ __device__ __forceinline__ void ifc_tile(const ZArgs& z, c2<T>* __restrict__ spe
     }
 }
 
-// Interface factors of pair s (plan time; thread per pair, kc <= 64 rows of
-// scratch per thread in LDS at [i][thread]): the coefficients (A, C) of the
-// first and last row of every chunk, from the same sweeps as the y tiles,
-// then the Thomas factors c'_r = C_r / den_r, 1/den_r with
-// den_r = 1 - A_r c'_{r-1} (den_0 = 1), stored as the maps of the interface
-// scans: -A_r / den_r, -c'_r, 1 / den_r. Computed in FP64 whatever the
-// spectrum's precision and stored in it: for the near-singular low
-// wavenumber pairs den_r is a difference of nearly equal terms, and an FP32
+// Interface factors of pair s (plan time; a thread per pair): the coefficients of
+// the first and last row of every chunk, from the same sweeps as the y tiles, then
+// the Thomas factors, stored as the maps of the interface scans: -A_r / den_r,
+// -c'_r = -C_r / den_r, 1 / den_r with den_r = 1 + A_r (-c'_{r-1}) (den_0 = 1).
+//
+// Without cancellation. Every row is x_i = al x_left + ga x_right (+ d), al and
+// ga >= 0, and what they lack of 1, sg = 1 - al - ga, is carried along instead of
+// being formed: it starts as -(a + b + c) / -b, which is next to the eigenvalue
+// sum over b (the sums' rounding errors are taken in exactly, so it belongs to
+// the rounded b that the tiles use), and every pivot is a sum of positive terms,
+//     1 - ga' al = (al + sg) + ga (ga' + sg')  for ga' = 1 - al' - sg', and so on.
+// As differences the pivots lose the low wavenumbers' sg, whose reciprocal is the
+// solve's amplification there: 3.5e-14 of the lowest mode at 128 rows in chunks of
+// 8 and 2.2e-14 of 16, 2e-13 to 3e-13 at 1024 rows; summed, 1e-15 to 2e-15 (against
+// extended precision). Computed in FP64 whatever the spectrum's precision: an FP32
 // recurrence would spoil the corrections of the mixed refinement (256x256x512
 // tanh grid: relres 1.8e-10 after one sweep, against 1.1e-11 with the FP64
 // table).
-template <typename T>
-__device__ __forceinline__ void ifc_table_pair(const ZArgs& z, int s, T* tab, c2<double>* scratch,
-                                               int sstride) {
-    using C = c2<double>;
+template <typename T, int KC>
+__device__ __forceinline__ void ifc_table_pair(const ZArgs& z, int s, T* tab) {
     const int S = z.mx * z.ny;
     const IfcShape h = ifc_shape(z.nc, S);
     const int m = s / z.ny, n = s - m * z.ny;
     const double lam = z.lamx[m] + z.lamy[n];
-    const int kc = z.kc;
-    double cprev = 0.0;
+    struct Row {
+        double al, ga, sg;
+    };
+    double t = 0.0;  // 1 + c'_{r-1}
     for (int c = 0; c < z.nc; ++c) {
-        const int k0 = c * kc;
-        double aa = 0.0, cc = 0.0;
-        for (int i = 0; i < kc; ++i) {
-            const ZRow row = zrow(z, k0 + i, lam);
-            double na, ncc;
-            (void)chunk_fwd<double>(i, row, aa, cc, na, ncc);
-            scratch[i * sstride] = C{na, ncc};
-            aa = na;
-            cc = ncc;
-        }
-        const C w0 = scratch[0];
-        const C wl = scratch[(kc - 1) * sstride];
-        double A0 = w0.x, C0 = w0.y;
-        if (kc >= 3) {
-            double ab = scratch[(kc - 2) * sstride].x, cb = scratch[(kc - 2) * sstride].y;
-            for (int i = kc - 3; i >= 1; --i) {
-                const C wi = scratch[i * sstride];
-                chunk_bwd<double>(wi.x, wi.y, ab, cb);
+        ZRow w[KC];
+#pragma unroll
+        for (int i = 0; i < KC; ++i) w[i] = zrow(z, c * KC + i, 0.0);  // lam is added below
+        Row q[KC];
+#pragma unroll
+        for (int i = 0; i < KC; ++i) {
+            const double a = w[i].a, b0 = w[i].b, cc = w[i].c;
+            // a + cc = u + eu, b0 + lam = b + eb, exactly
+            const double u = a + cc, ua = u - a, eu = (a - (u - ua)) + (cc - ua);
+            const double b = b0 + lam, bl = b - b0, eb = (b0 - (b - bl)) + (lam - bl);
+            const double sg = ((eb - eu) - (u + b0)) - lam;  // -(a + b + cc)
+            if (i < 2) {
+                const double r = rcp_nr(-b);
+                q[i] = Row{a * r, cc * r, sg * r};
+            } else {
+                const double r = rcp_nr((cc + sg) + a * (q[i - 1].al + q[i - 1].sg));
+                q[i] = Row{a * q[i - 1].al * r, cc * r, (sg + a * q[i - 1].sg) * r};
             }
-            const double r0 = chunk_row0_pivot<double>(w0.y, ab);
-            A0 = w0.x * r0;
-            C0 = -w0.y * cb * r0;
+            if (c * KC + i >= z.nz) q[i] = Row{0.0, 0.0, 1.0};  // identity rows
         }
-        const double rowA[2] = {A0, wl.x};
-        const double rowC[2] = {C0, wl.y};
+        const Row last = q[KC - 1];
+        Row b = q[KC - 2];
+#pragma unroll
+        for (int i = KC - 3; i >= 1; --i)
+            b = Row{q[i].al + q[i].ga * b.al, q[i].ga * b.ga, q[i].sg + q[i].ga * b.sg};
+        const Row f = q[0];
+        const double r0 = rcp_nr((f.al + f.sg) + f.ga * (b.ga + b.sg));
+        const Row first{f.al * r0, f.ga * b.ga * r0, (f.sg + f.ga * b.sg) * r0};
+#pragma unroll
         for (int e = 0; e < 2; ++e) {
+            const Row x = e == 0 ? first : last;
             const int r = 2 * c + e;
-            const double inv = r == 0 ? 1.0 : 1.0 / (1.0 - rowA[e] * cprev);
-            cprev = rowC[e] * inv;
-            tab[ifc_tab_index(h, s, r, 0)] = (T)(-rowA[e] * inv);
-            tab[ifc_tab_index(h, s, r, 1)] = (T)(r < h.R - 1 ? -cprev : 0.0);
+            const double inv = r == 0 ? 1.0 : 1.0 / ((x.ga + x.sg) + x.al * t);
+            t = (x.sg + x.al * t) * inv;
+            tab[ifc_tab_index(h, s, r, 0)] = (T)(x.al * inv);
+            tab[ifc_tab_index(h, s, r, 1)] = (T)(r < h.R - 1 ? x.ga * inv : 0.0);
             tab[ifc_tab_index(h, s, r, 2)] = (T)inv;
         }
     }
