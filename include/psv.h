@@ -288,10 +288,11 @@ psv_status psv_solve_converged_adjoint(psv_plan* plan, const double* w, const do
  * scalars and flags with kernels. The call allocates nothing, on the host or
  * the device, and records no memset. Arguments and results as psv_solve
  * (FP64, built-in launch shapes: the same passes and bits as a plan created
- * with autotune = 0), without info. opts may be NULL (defaults); it must have
+ * with autotune = 0; where the built-in chunk rows leave no room for the
+ * factors, the next of 8 and 16 that do, as a plan of those), without info. opts may be NULL (defaults); it must have
  * precision PSV_FP64, autotune 0 and check_inputs 0 (PSV_ERR_INVALID_ARG);
  * chunk_rows and x_stencil are honoured. Tables and workspace must fit the
- * array (about 5 million cells; 128^3 takes about 24 MB of it):
+ * array (5.4 to 7 million cells; 128^3 takes about 24 MB of it):
  * PSV_ERR_UNSUPPORTED_SIZE otherwise, before any device work when the
  * spectrum alone is too large. Every call on one GPU shares that GPU's array:
  * calls that overlap in time on one GPU (other streams, other threads) race

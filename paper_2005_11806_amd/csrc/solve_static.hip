@@ -113,7 +113,11 @@ void solve_static(const psv_grid& grid, const psv_opts& o, const double* f, cons
     // the spectrum alone: rejected before any device work
     if (P.nspec() * sizeof(double2) > STATIC_BYTES)
         fail(PSV_ERR_UNSUPPORTED_SIZE, "grid too large for the static scratch array (64 MiB)");
-    const int kc = builtin_shape(P);
+    int kc = builtin_shape(P);
+    // twice the chunk rows halve the interface factors: those take a grid that
+    // the built-in ones leave no room for (unless the caller fixed them)
+    for (int c : {8, 16})
+        if (!o.chunk_rows && c > kc && layout(P, kc).total > STATIC_BYTES && kc_fits(P, c)) kc = c;
     const Layout L = layout(P, kc);
     if (L.total > STATIC_BYTES)
         fail(PSV_ERR_UNSUPPORTED_SIZE, "tables and workspace exceed the static scratch array (64 MiB)");
