@@ -212,9 +212,18 @@ int builtin_shape(Plan& p) {
     if (x_lds_max(p.nx, p.lp.lbx) > (size_t)std::min(lds_max, LDS_MAX_BLOCK))
         fail(PSV_ERR_UNSUPPORTED_SIZE, "line length exceeds the LDS budget");
     p.lp.lbx_inv = p.lp.lbx;
-    // FP64 inverse, 8 lines (whole 128-byte lines of bins) where they are two
-    // full steps of the block: 256x256x512 81 us against 89 at 4
-    if (p.opts.precision == PSV_FP64 && p.nx == 256 && p.ny % 8 == 0) p.lp.lbx_inv = 8;
+    // FP64 inverse: a tile of 8 lines writes and reads whole 128-byte lines of bins.
+    // It is taken where its pairs of bins fill every step of the block, in two steps at
+    // most, and there are three tiles per CU: half-length 128 at 8192 tiles 42.0 us
+    // against 43.5 at 4 lines, 1024 tiles 7.2 against 8.4, 768 6.3 and 6.4, but 256
+    // tiles 5.2 and 4.9. Partly filled steps lose as often as they win (8 lines
+    // against the forward pass's at 33 and at 4 million cells: half-length 72 0.94 and
+    // 1.07 of the time, 96 0.94 and 1.09, 108 1.09 and 1.17, 144 1.14 and 1.34); FP32
+    // is indifferent (128: 1.04 and 0.94).
+    const int half = 8 * (p.nx / 2) / 2;  // pairs of bins of 8 lines, one per thread and step
+    if (p.opts.precision == PSV_FP64 && p.ny % 8 == 0 && half % 256 == 0 && half <= 2 * 256 &&
+        (size_t)(p.ny / 8) * p.nz >= 3 * 256)
+        p.lp.lbx_inv = 8;
     p.lp.xstage = p.opts.x_stencil == 2 ? 0 : 1;
     const size_t csz = p.opts.precision == PSV_MIXED ? sizeof(float2) : sizeof(double2);
     int kc = p.opts.chunk_rows;
