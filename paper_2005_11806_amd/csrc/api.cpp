@@ -257,7 +257,7 @@ psv_status psv_plan_set_shape(psv_plan* plan, const psv_shape* shape) {
         Plan& P = plan->p;
         const psv_shape& h = *shape;
         for (int lb : {h.lines_x, h.lines_x_inv})
-            need(lb >= 1 && lb <= 64 && P.ny % lb == 0, "lines per x block must divide ny (1..64)");
+            need(lb >= 1 && lb <= psv::MAX_LINES_X && P.ny % lb == 0, "lines per x block must divide ny (1..64)");
         need(h.chunk_rows == 4 || h.chunk_rows == 8 || h.chunk_rows == 16, "chunk_rows must be 4, 8 or 16");
         need(h.x_staged == 0 || h.x_staged == 1, "x_staged must be 0 or 1");
         need(h.x_order == 0 || h.x_order == 1, "x_order must be 0 or 1");

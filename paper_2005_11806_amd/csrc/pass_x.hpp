@@ -49,7 +49,7 @@ __host__ __device__ constexpr int x_sep(int M, int dir) {
 #undef PSV_CASE
     return 1;
 }
-inline bool x_compiled(int M) {
+constexpr bool x_compiled(int M) {
     switch (M) {
 #define PSV_CASE(n) case n:
         PSV_X_SIZES(PSV_CASE)
@@ -70,7 +70,7 @@ inline bool x_compiled(int M) {
 // and 13 at 146). Runtime lengths: plain lines, M apart.
 template <int N>
 using XLayout = std::conditional_t<(N > 0), Pad8, NoPad>;
-__host__ __device__ inline int x_line_span(int M, int lb) {
+__host__ __device__ constexpr int x_line_span(int M, int lb) {
     const int want = lb >= 8 ? 1 : 8 / lb;  // modulo 8
     int s = M + M / 8;
     if (lb > 1)
@@ -86,31 +86,60 @@ __host__ __device__ inline int x_line_span(int M, int lb) {
 // buffers. One of these takes the rows' place once they are used up; in a
 // tile whose threads make one step each over it (x_one_step) both do, behind
 // a barrier: 27 instead of 36 KiB at 256 x 4 lines, five blocks per CU.
-inline size_t x_rows_bytes(int nx, int lb, bool stage, int fields) {
-    return stage ? (size_t)fields * (lb + 2) * nx * sizeof(double) : 0;
+constexpr size_t x_rows_bytes(int M, int lb, bool stage, int fields) {
+    return stage ? (size_t)fields * (lb + 2) * 2 * M * sizeof(double) : 0;
 }
-__host__ __device__ inline bool x_one_step(int M, int lb, int nt) { return lb * (M / 2) <= nt; }
-inline size_t fwd_x_lds(const XGeom& g, size_t csz, int mode, bool ct, int nt = 256) {
+__host__ __device__ constexpr bool x_one_step(int M, int lb, int nt) { return lb * (M / 2) <= nt; }
+// Elements from one line to the next
+constexpr int x_span(int M, int lb) { return x_compiled(M) ? x_line_span(M, lb) : M; }
+constexpr size_t fwd_x_bytes(int M, int lb, bool stage, size_t csz, int mode, bool ct, int nt = 256) {
     const int fields = mode == FWD_CONST ? 0 : (mode == FWD_RESID ? 1 : 2);
-    const size_t rows = x_rows_bytes(g.nx, g.lb, g.stage != 0, fields);
-    const size_t buf = (size_t)g.lb * (ct ? g.ls : g.M) * csz;
-    const size_t tw = (size_t)(ct ? 1 : 2) * g.M * csz + 16;
-    if (ct && rows && x_one_step(g.M, g.lb, nt)) return tw + (rows > 2 * buf ? rows : 2 * buf);
+    const size_t rows = x_rows_bytes(M, lb, stage, fields);
+    const size_t buf = (size_t)lb * (ct ? x_span(M, lb) : M) * csz;
+    const size_t tw = (size_t)(ct ? 1 : 2) * M * csz + 16;
+    if (ct && rows && x_one_step(M, lb, nt)) return tw + (rows > 2 * buf ? rows : 2 * buf);
     return tw + buf + (rows > buf ? rows : buf);
 }
-inline size_t inv_x_lds(const XGeom& g, size_t csz, bool ct) {
-    if (ct) return ((size_t)2 * g.lb * g.ls + g.M) * csz;
-    return ((size_t)g.lb * g.M + (size_t)g.lb * (g.M + 1) + 2 * (size_t)g.M) * csz;
+constexpr size_t inv_x_bytes(int M, int lb, size_t csz, bool ct) {
+    if (ct) return ((size_t)2 * lb * x_span(M, lb) + M) * csz;
+    return ((size_t)lb * M + (size_t)lb * (M + 1) + 2 * (size_t)M) * csz;
 }
-// Bound that decides which lines per block fit (FP64, forward with staged
-// rows or inverse, whichever is larger)
-inline size_t x_lds_max(int nx, int lb) {
+inline size_t fwd_x_lds(const XGeom& g, size_t csz, int mode, bool ct) {
+    return fwd_x_bytes(g.M, g.lb, g.stage != 0, csz, mode, ct);
+}
+inline size_t inv_x_lds(const XGeom& g, size_t csz, bool ct) { return inv_x_bytes(g.M, g.lb, csz, ct); }
+// Which lines per block are admitted and chosen from: by FP64 tiles (forward with
+// staged rows or inverse, whichever is larger) of lines M + M / 8 apart, a figure
+// that saved and given shapes are held against. The tiles themselves come to a
+// little more or less (their lines' spans against no second set of twiddles);
+// x_admitted_fit below checks that whatever is admitted fits a block.
+constexpr size_t x_lds_max(int nx, int lb) {
     const size_t M = nx / 2, csz = 16, span = (size_t)lb * M + (size_t)lb * M / 8 + 1;
-    const size_t rows = x_rows_bytes(nx, lb, true, 2), buf = span * csz;
+    const size_t rows = x_rows_bytes(nx / 2, lb, true, 2), buf = span * csz;
     const size_t a = buf + 2 * M * csz + 16 + (rows > buf ? rows : buf);
     const size_t half = (size_t)lb * (M + 1);
     const size_t b = (span + (half > span ? half : span) + 2 * M) * csz;
     return a > b ? a : b;
+}
+constexpr int MAX_LINES_X = 64;  // lines per block that a shape may ask for
+constexpr bool smooth23(int n) {
+    while (n % 2 == 0) n /= 2;
+    while (n % 3 == 0) n /= 3;
+    return n == 1;
+}
+constexpr bool x_admitted_fit() {
+    for (int nx = 4; nx <= 1024; nx += 2) {
+        for (int lb = 1; lb <= MAX_LINES_X; ++lb) {  // (a divisor of ny)
+            if (!smooth23(nx) || !smooth23(lb) || x_lds_max(nx, lb) > (size_t)LDS_MAX_BLOCK) continue;
+            for (int ct = 0; ct <= (x_compiled(nx / 2) ? 1 : 0); ++ct) {  // a batch's tiles may be runtime ones
+                if (inv_x_bytes(nx / 2, lb, 16, ct) > (size_t)LDS_MAX_BLOCK) return false;
+                for (int mode : {FWD_CONST, FWD_METHOD1, FWD_RESID, FWD_METHOD3})
+                    for (int stage = 0; stage <= 1; ++stage)
+                        if (fwd_x_bytes(nx / 2, lb, stage, 16, mode, ct) > (size_t)LDS_MAX_BLOCK) return false;
+            }
+        }
+    }
+    return true;
 }
 
 // (1 - rho0/rho_f) (p_R - p_L) across the face between cells L and R, with
@@ -936,7 +965,7 @@ inline XGeom make_xgeom(const Plan& p, bool inverse = false) {
     g.M = p.nx / 2;
     g.lb = inverse ? p.lp.lbx_inv : p.lp.lbx;
     g.tiles = p.ny / g.lb;
-    g.ls = x_compiled(g.M) ? x_line_span(g.M, g.lb) : g.M;
+    g.ls = x_span(g.M, g.lb);
     g.by_tiles = fast_div(g.tiles);
     g.by_lb = fast_div(g.lb);
     g.by_m = fast_div(g.M);

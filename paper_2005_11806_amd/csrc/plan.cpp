@@ -11,6 +11,8 @@
 
 namespace psv {
 
+static_assert(x_admitted_fit(), "an x tile that a shape may ask for exceeds the LDS of a block");
+
 [[noreturn]] void fail(psv_status s, const std::string& msg) { throw Error{s, msg}; }
 
 void hip_check(hipError_t e, const char* what) {
