@@ -230,14 +230,9 @@ __host__ __device__ constexpr int radix_prefix(RadixList L, int s) {
     return p;
 }
 
-// LDS layouts of FFT lines: contiguous, or with one pad element after every 8
-// (the radix-R scatter of a Stockham stage then spreads over the banks
-// instead of hitting the same ones); element i lives at at(i).
-struct NoPad {
-    __host__ __device__ static constexpr int at(int i) { return i; }
-    __host__ __device__ static constexpr bool linear(int) { return true; }
-    __host__ __device__ static constexpr int step(int s) { return s; }
-};
+// LDS layout of the compile-time FFT lines: one pad element after every 8 (the
+// radix-R scatter of a Stockham stage then spreads over the banks instead of
+// hitting the same ones); element i lives at at(i).
 struct Pad8 {
     __host__ __device__ static constexpr int at(int i) { return i + (i >> 3); }
     // at(i + k s) = at(i) + k step(s) whenever s is a multiple of 8, so the
@@ -257,7 +252,7 @@ __device__ __forceinline__ void bfly_ct(C* v) {
 // Butterfly j of a radix-R Stockham stage (NS = product of the earlier
 // radices, NB = N / R) of the line at in: load with
 // twiddles and transform into v, then store.
-template <int R, int DIR, int NS, int NB, int TSTEP, int SEP, typename P = NoPad, typename C>
+template <int R, int DIR, int NS, int NB, int TSTEP, int SEP, typename P, typename C>
 __device__ __forceinline__ void stockham_load_ct(const C* __restrict__ in, int j,
                                                  const C* __restrict__ tw, C* v) {
     if constexpr (P::linear(NB)) {
@@ -283,7 +278,7 @@ __device__ __forceinline__ void stockham_load_ct(const C* __restrict__ in, int j
 // The outputs of a butterfly in an early stage (NS divides 8, NS R is a
 // multiple of 8) are constant offsets apart in either layout: the first lies
 // at a multiple of 8 plus j mod NS, so no other crosses a group of 8 by it.
-template <int R, int NS, typename P = NoPad, typename C>
+template <int R, int NS, typename P, typename C>
 __device__ __forceinline__ void stockham_store_ct(C* __restrict__ out, int j, const C* v) {
     const int base = (j / NS) * NS * R + j % NS;
     if constexpr (P::linear(NS)) {

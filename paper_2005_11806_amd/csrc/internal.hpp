@@ -298,9 +298,6 @@ void launch_divergence_rhs(const Plan& p, const double* ux, const double* uy, co
 void launch_correct_velocity(const Plan& p, const double* ux, const double* uy, const double* uz,
                              const double* pr, const double* rho, double dt, double* ox,
                              double* oy, double* oz, hipStream_t s);
-// out = sum of partials[0 .. nblocks)
-void launch_sum_partials(const Plan& p, const double* partials, int nblocks, double* out,
-                         hipStream_t s);
 // Method III loop control on the device: clear the loop flags; after each
 // forward pass, eps = dt * sum(partials) goes to S_EPS (S_EPS0 without a
 // pressure iterate); flags[F_DONE] is set once eps <= eps_t (F_CONV too) or

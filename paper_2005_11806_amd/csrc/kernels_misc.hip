@@ -709,13 +709,6 @@ void launch_m3_reset(const Plan& p, hipStream_t s) {
     PSV_HIP(hipGetLastError());
 }
 
-void launch_sum_partials(const Plan& p, const double* partials, int nblocks, double* out,
-                         hipStream_t s) {
-    const double* src = stage_partials(p, partials, nblocks, 1, nullptr, s);
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(RB), 0, s, src, nblocks, 1, out);
-    PSV_HIP(hipGetLastError());
-}
-
 void launch_adjoint_faces(const Plan& p, const double* x, const double* f, const double* rho,
                           const double* pprev, const double* rho0, double* grad_f,
                           double* grad_rho, double* grad_p, double* partials, hipStream_t s) {

@@ -68,8 +68,6 @@ constexpr bool x_compiled(int M) {
 // stride of 8 / lb modulo 8 puts those on different banks (a stride of 144
 // elements, 4 lines: 16 cycles per read and 32 per write of a wave against 9
 // and 13 at 146). Runtime lengths: plain lines, M apart.
-template <int N>
-using XLayout = std::conditional_t<(N > 0), Pad8, NoPad>;
 __host__ __device__ constexpr int x_line_span(int M, int lb) {
     const int want = lb >= 8 ? 1 : 8 / lb;  // modulo 8
     int s = M + M / 8;

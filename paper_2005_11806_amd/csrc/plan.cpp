@@ -200,7 +200,7 @@ static int lines_x(const Plan& p, size_t budget) {
 // set): 8 where two of its y tiles fit a CU (256x256x512 z solve: 218 us
 // against 294 at 4 rows, twice the interface systems, and 214 at 16; 128^3 26.5
 // against 29.0 and 27.0; 64^3 14.7, 14.7 and 16.5), else 4 (128x486x96, a
-// runtime length: 134 us against 187 at 8), else the largest that fits. FP32
+// runtime length: 134 us against 187 at 8). FP32
 // spectra: the largest of 16, 8, 4 whose tile takes at most 48 KiB as the
 // batched kernels lay it out. Their z solve hardly depends on the rows
 // (256x256x512: 55 us at 16 rows, 57 at 8; 128^3 17.1 and 16.3), while the
@@ -239,9 +239,7 @@ int builtin_shape(Plan& p) {
             if (!kc && kc_fits(p, c)) kc = c;
     for (int c : {8, 4})
         if (!kc && kc_fits(p, c) && 2 * yz_lds(p.ny, c, csz, yz_compiled(p.ny)) <= 160 * 1024) kc = c;
-    if (!kc)
-        for (int c : {4, 8, 16})
-            if (!kc && kc_fits(p, c)) kc = c;
+    if (!kc && kc_fits(p, 4)) kc = 4;
     if (!kc) fail(PSV_ERR_UNSUPPORTED_SIZE, "y lines exceed the LDS of a block");
     return kc;
 }
