@@ -828,43 +828,47 @@ __device__ __forceinline__ void inv_x_tile_ct(const XGeom& g, const c2<TC>* __re
     C* tw = buf1 + lb * ls;  // exp(-2 pi i t / M), t < M
     const c2<TS>* sk = spec + (size_t)k * ((size_t)g.mx * g.ny) + j0;
     const int ntask = lb * H;
-    constexpr int TWP = (M + NT - 1) / NT;
-    C twr[TWP];
+    struct Bins {
+        C w, xm, xc, xh;
+    };
     auto bins = [&](int t) {
         const int m = fdiv(t, g.by_lb), line = t - m * lb;
-        const C w = tw_g[m];
-        C xm = cconv<C>(at_off(sk, (unsigned)(m * g.ny + line)));
-        C xc = cconv<C>(at_off(sk, (unsigned)((M - m) * g.ny + line)));
-        C xh{(TC)0, (TC)0};
-        if (m == 0) xh = cconv<C>(at_off(sk, (unsigned)(H * g.ny + line)));
-        if (t == (int)threadIdx.x) {  // behind the first round's bins
-#pragma unroll
-            for (int i = 0; i < TWP; ++i) {
-                const int e = (int)threadIdx.x + NT * i;
-                twr[i] = tw_g[2 * (e < M ? e : 0)];
-            }
-        }
+        Bins q;
+        q.w = tw_g[m];
+        q.xm = cconv<C>(at_off(sk, (unsigned)(m * g.ny + line)));
+        q.xc = cconv<C>(at_off(sk, (unsigned)((M - m) * g.ny + line)));
+        q.xh = C{(TC)0, (TC)0};
+        if (m == 0) q.xh = cconv<C>(at_off(sk, (unsigned)(H * g.ny + line)));
+        return q;
+    };
+    auto put = [&](int t, const Bins& q) {
+        const int m = fdiv(t, g.by_lb), line = t - m * lb;
+        C xm = q.xm, xc = q.xc;
         if (m == 0) xm.y = xc.y = (TC)0;
         const C e = C{(TC)0.5 * (xm.x + xc.x), (TC)0.5 * (xm.y - xc.y)};
         const C d = C{(TC)0.5 * (xm.x - xc.x), (TC)0.5 * (xm.y + xc.y)};
-        const C o = cmul_sep<SEP>(d, cconj(w));
+        const C o = cmul_sep<SEP>(d, cconj(q.w));
         C* zl = buf0 + line * ls;
         zl[P::at(m)] = C{e.x - o.y, e.y + o.x};
-        zl[P::at(m == 0 ? H : M - m)] = m == 0 ? cconj(xh) : C{e.x + o.y, o.x - e.y};
+        zl[P::at(m == 0 ? H : M - m)] = m == 0 ? cconj(q.xh) : C{e.x + o.y, o.x - e.y};
     };
-    if ((int)threadIdx.x < ntask) {
-        bins((int)threadIdx.x);
-    } else {
-#pragma unroll
-        for (int i = 0; i < TWP; ++i) {
-            const int e = (int)threadIdx.x + NT * i;
-            twr[i] = tw_g[2 * (e < M ? e : 0)];
-        }
-    }
-    for (int t = (int)threadIdx.x + NT; t < ntask; t += NT) bins(t);
+    const int tid = (int)threadIdx.x;
+    Bins first;
+    if (tid < ntask) first = bins(tid);
+    // twiddles behind the first bins, outside any branch: there an array of them
+    // goes to scratch memory (1024x64x48 step: 100 us, 97 without)
+    constexpr int TWP = (M + NT - 1) / NT;
+    C twr[TWP];
 #pragma unroll
     for (int i = 0; i < TWP; ++i) {
-        const int e = (int)threadIdx.x + NT * i;
+        const int e = tid + NT * i;
+        twr[i] = tw_g[2 * (e < M ? e : 0)];
+    }
+    if (tid < ntask) put(tid, first);
+    for (int t = tid + NT; t < ntask; t += NT) put(t, bins(t));
+#pragma unroll
+    for (int i = 0; i < TWP; ++i) {
+        const int e = tid + NT * i;
         if (e < M) tw[e] = twr[i];
     }
     __syncthreads();

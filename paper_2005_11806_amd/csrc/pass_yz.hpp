@@ -276,6 +276,14 @@ __device__ __forceinline__ void yz_fwd_tile_ct(const ZArgs& z, c2<T>* __restrict
             const int e = (int)threadIdx.x + i * NT;
             twr[i] = tw_g[e < N ? e : 0];
         }
+        auto put_tw = [&] {
+#pragma unroll
+            for (int i = 0; i < TWP; ++i) {
+                const int e = (int)threadIdx.x + i * NT;
+                if (e < N) tw[e] = twr[i];
+            }
+        };
+        if constexpr (TWP > 1) put_tw();
 #pragma unroll
         for (int it = 0; it < IT; ++it) {
             const int t = (int)threadIdx.x + it * NT;
@@ -289,11 +297,7 @@ __device__ __forceinline__ void yz_fwd_tile_ct(const ZArgs& z, c2<T>* __restrict
                 stockham_store_ct<R, 1, P>(buf + line * LS, j, v[it]);
             }
         }
-#pragma unroll
-        for (int i = 0; i < TWP; ++i) {
-            const int e = (int)threadIdx.x + i * NT;
-            if (e < N) tw[e] = twr[i];
-        }
+        if constexpr (TWP == 1) put_tw();
     }
     __syncthreads();
     fft_inplace<N, 1, RL.count, -1, KC, LS, NT, SEP, P>(buf, tw);
@@ -330,33 +334,58 @@ __device__ __forceinline__ void yz_inv_tile_ct(const ZArgs& z, c2<T>* __restrict
     C* tw = buf + KC * LS;
     const YzTile<T> t0(z, N, KC, spec, b);
     C twr[TWP];
-    for (int n = threadIdx.x; n < N; n += NT) {
-        C d[KC];
+    auto load_tw = [&] {
+#pragma unroll
+        for (int i = 0; i < TWP; ++i) {
+            const int e = (int)threadIdx.x + i * NT;
+            twr[i] = tw_g[e < N ? e : 0];
+        }
+    };
+    auto put_tw = [&] {
+#pragma unroll
+        for (int i = 0; i < TWP; ++i) {
+            const int e = (int)threadIdx.x + i * NT;
+            if (e < N) tw[e] = twr[i];
+        }
+    };
+    auto rows = [&](int n, C (&d)[KC]) {
 #pragma unroll
         for (int i = 0; i < KC; ++i) {
             const C v = at_off(t0.base + (i < t0.nl ? i : 0) * t0.SP, (unsigned)n);
             d[i] = i < t0.nl ? v : C{(T)0, (T)0};
         }
-        if (n == (int)threadIdx.x) {  // behind the first system's rows
-#pragma unroll
-            for (int i = 0; i < TWP; ++i) {
-                const int e = (int)threadIdx.x + i * NT;
-                twr[i] = tw_g[e < N ? e : 0];
-            }
-        }
+    };
+    auto put = [&](int n, C (&d)[KC]) {
         if (t0.m != 0 || n != 0)
             chunk_substitute<T, KC>(zrows(z, t0.k0, z.lamx[t0.m] + z.lamy[n]), t0.nl, d);
         C* col = buf + P::at(n);
 #pragma unroll
         for (int i = 0; i < KC; ++i) col[i * LS] = d[i];
-    }
-    if constexpr (N < NT) {
-        if ((int)threadIdx.x >= N) twr[0] = C{(T)0, (T)0};
-    }
-#pragma unroll
-    for (int i = 0; i < TWP; ++i) {
-        const int e = (int)threadIdx.x + i * NT;
-        if (e < N) tw[e] = twr[i];
+    };
+    // the twiddles are loaded behind the first system's rows
+    if constexpr (TWP > 1) {
+        // and stored before the substitution: several of them across its branch go
+        // to scratch memory (64x1024x48 step: 99 us, 96 without)
+        C first[KC];
+        rows((int)threadIdx.x, first);
+        load_tw();
+        put_tw();
+        put((int)threadIdx.x, first);
+        for (int n = (int)threadIdx.x + NT; n < N; n += NT) {
+            C d[KC];
+            rows(n, d);
+            put(n, d);
+        }
+    } else {
+        if ((int)threadIdx.x < N) {
+            C d[KC];
+            rows((int)threadIdx.x, d);
+            load_tw();
+            put((int)threadIdx.x, d);
+        } else {
+            twr[0] = C{(T)0, (T)0};
+        }
+        put_tw();
     }
     __syncthreads();
     fft_inplace<N, 0, LAST, +1, KC, LS, NT, SEP, P>(buf, tw);
