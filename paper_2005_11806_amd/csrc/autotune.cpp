@@ -154,7 +154,10 @@ void autotune_plan(Plan& p) {
     auto it = g_cache.find(key);
     const bool kc_fixed = p.opts.chunk_rows != 0;
     if (it != g_cache.end()) {
-        if (fits_x(p, it->second.lbx) && fits_x(p, it->second.lbx_inv) &&
+        // (the built-in counts may lie past the candidates' bound: one line at
+        // nx = 1024, 8 lines of the inverse pass at nx = 256)
+        auto takes = [&](int lb, int built_in) { return lb == built_in || fits_x(p, lb); };
+        if (takes(it->second.lbx, p.lp.lbx) && takes(it->second.lbx_inv, p.lp.lbx_inv) &&
             kc_fits(p, it->second.kc)) {
             p.lp.lbx = it->second.lbx;
             p.lp.lbx_inv = it->second.lbx_inv;

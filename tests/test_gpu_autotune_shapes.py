@@ -15,3 +15,17 @@ def test_counts_that_are_no_power_of_two(gpu, tmp_path, monkeypatch):
     built_in, tuned = gpu.Plan(grid).get_shape(), gpu.Plan(grid, autotune=2).get_shape()
     say(f"built-in {built_in}, tuned {tuned}")
     assert tuned["lines_x"] in (3, 6) and tuned["lines_x_inv"] in (3, 6)
+
+
+@pytest.mark.parametrize("nx,ny,nz", [(1024, 8, 6), (256, 64, 96)])
+def test_choice_is_found_again(gpu, tmp_path, monkeypatch, nx, ny, nz):
+    """A tuned shape that is the built-in one, with more LDS than the other
+    candidates may take, is read back: the second plan does not tune again."""
+    cache = tmp_path / "tune.txt"
+    monkeypatch.setenv("PSV_AUTOTUNE_CACHE", str(cache))
+    grid = gpu.Grid(nx, ny, nz, 1.0, 1.0, 1.0)
+    first = gpu.Plan(grid, autotune=2).get_shape()
+    second = gpu.Plan(grid, autotune=2).get_shape()
+    say(f"{nx}x{ny}x{nz} {first}: {cache.read_text()}")
+    assert second == first
+    assert len([ln for ln in cache.read_text().splitlines() if f":{nx}x{ny}x{nz}:" in ln]) == 1
