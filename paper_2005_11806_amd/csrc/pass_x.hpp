@@ -35,11 +35,18 @@ struct Stencil {
 // The batched kernels hold those up to 128 of the first list.
 #define PSV_X_SIZES(X) X(16) X(24) X(32) X(48) X(64) X(96) X(128) X(192) X(256) X(512)
 #define PSV_X_MORE(X) X(8) X(12) X(18) X(36) X(54) X(72) X(108) X(144) X(162) X(384)
+// The second list holds further lengths of small and middle size that are in use. In
+// neither, and so 1.5 to 3 times slower: odd half-lengths (nx = 6, 18, 54, 162, 486),
+// nx of 4, 8 and 12, and 432, 576, 648, 864, 972.
+//
 // How FP32 transforms round their twiddle products (cmul_sep): a refined or
-// iterated result keeps 1e-10 of that rounding. Lengths of the second list take
-// the runtime transform's way (which a batch takes for them), the others what
-// the compiler makes of them but for two whose choice is written out. dir: -1
-// forward, +1 inverse.
+// iterated result keeps 1e-10 of that rounding. In the second list it is written
+// out, the runtime transform's way (which a batch takes for these lengths), and so it
+// is in the forward ones of 64 and 512, which would otherwise not round as they did
+// in an earlier form of the tile. The rest of the first list is left to the compiler,
+// which fuses some stages one way and some the other (neither form written out
+// throughout gives the bits of any of them): another compiler may round those
+// differently. dir: -1 forward, +1 inverse.
 template <typename T>
 __host__ __device__ constexpr int x_sep(int M, int dir) {
     if (sizeof(T) == 8) return 0;
@@ -335,11 +342,13 @@ __device__ __forceinline__ int staged_line(const XGeom& g, int j0, int rr) {
 // directly, where the caches serve the rows that neighbouring tiles share.
 // After the remaining stages a thread reads Z_m and Z_(N-m) once and writes
 // both bins they determine. Against every stage and the split of each bin
-// through LDS, that is 391 instead of 607 vector instructions and 228 instead of
-// 300 LDS cycles per wave, 96 registers and 27 KiB (five blocks per CU instead
-// of four): 250 -> 233 us per pass at 256x256x512 FP64 (1.08 GB; without its
-// transform it takes as long, so memory bounds it: 210 us with contiguous
-// spectrum stores, 175 without stores), 21.2 -> 18.1 at 128^3.
+// through LDS, that is 346 instead of 607 vector and 36 instead of 43.5 LDS
+// instructions per wave (counters) and 27 KiB at 256 x 4 lines: 250 -> 233 us per
+// pass at 256x256x512 FP64 (1.08 GB; without its transform it takes as long, so
+// memory bounds it: 210 us with contiguous spectrum stores, 175 without stores),
+// 21.2 -> 18.1 at 128^3. Registers (METHOD1): 96 at half-length 128 and 93 to 95 at
+// lengths with a factor of 3, five waves per SIMD; 97 to 99 at the other powers of
+// two, and 99 to 106 in METHOD3, four.
 template <typename TC, typename TS, int MODE, int N, bool STAGE, int NT>
 __device__ __forceinline__ void fwd_x_tile_ct(const XGeom& g, const Stencil& st, const FwdArgs& a,
                                               const c2<TC>* __restrict__ tw_g,
@@ -807,9 +816,9 @@ __device__ __forceinline__ void inv_store(double2* out2, unsigned c, C v, double
 // field has real DC and Nyquist bins) and Z_{M/2} = conj X_{M/2}. The last
 // stage's butterflies store their outputs, neighbouring lanes neighbouring
 // pairs, without another pass through LDS. Against bins staged in LDS and every
-// stage through it: 124 instead of 224 vector instructions and 118 instead of
-// 232 LDS cycles per wave; 103 -> 90 us at 256x256x512 FP64 (540 MB, 6.0 TB/s),
-// 10.7 -> 7.1 at 128^3.
+// stage through it: 128 instead of 224 vector and 14.5 instead of 24.8 LDS
+// instructions per wave and step (counters); 103 -> 90 us at 256x256x512 FP64 and 4
+// lines, 83 at 8 (540 MB, 6.5 TB/s), 10.7 -> 7.1 at 128^3.
 template <typename TC, typename TS, int MODE, int N, int NT>
 __device__ __forceinline__ void inv_x_tile_ct(const XGeom& g, const c2<TC>* __restrict__ tw_g,
                                               const c2<TS>* __restrict__ spec,

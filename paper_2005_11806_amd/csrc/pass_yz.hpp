@@ -34,10 +34,10 @@
 
 namespace psv {
 
-// y-line lengths with a compile-time FFT; other lengths use the runtime FFT,
-// which ping-pongs between two buffers and takes 1.5 to 3 times as long
-// (512x384x96: 190 us per pass against 50). The batched kernels hold the first
-// list only.
+// y-line lengths with a compile-time FFT; other lengths (486, 576, 648, 864, 972 and
+// those below 16) use the runtime FFT, which ping-pongs between two buffers and
+// takes 1.5 to 3 times as long (512x384x96: 190 us per pass against 50). The batched
+// kernels hold the first list only.
 #define PSV_YZ_SIZES(X) X(32) X(48) X(64) X(96) X(128) X(192) X(256) X(512)
 #define PSV_YZ_MORE(X) \
     X(16) X(18) X(24) X(36) X(54) X(72) X(108) X(144) X(162) X(216) X(288) X(324) X(384) X(432) X(768) X(1024)
@@ -241,8 +241,8 @@ struct YzTile {
 // straight to it (a thread owns system n, so the lanes of a wave store 64
 // consecutive elements of a plane): between them the tile passes through LDS
 // once per further stage, in place. Against the whole tile staged in LDS first
-// and stored from it last: 59 instead of 91 LDS instructions and 402 instead of
-// 553 vector instructions per wave; 84.5 -> 82.5 us at 256x256x512 FP64 (541 MB,
+// and stored from it last: 59 instead of 91 LDS and 393 instead of 553 vector
+// instructions per wave (counters); 84.5 -> 82.5 us at 256x256x512 FP64 (541 MB,
 // 6.6 TB/s: memory bounds it), 13.4 -> 10.9 at 128^3 (kc 16), where latency does.
 template <typename T, int N, int KC, int NT>
 __device__ __forceinline__ void yz_fwd_tile_ct(const ZArgs& z, c2<T>* __restrict__ spec,

@@ -204,7 +204,9 @@ static int lines_x(const Plan& p, size_t budget) {
 // spectra: the largest of 16, 8, 4 whose tile takes at most 48 KiB as the
 // batched kernels lay it out. Their z solve hardly depends on the rows
 // (256x256x512: 55 us at 16 rows, 57 at 8; 128^3 17.1 and 16.3), while the
-// rounding of their sweeps, which does, shows at 1e-10 of a refined result.
+// rounding of their sweeps, which does, shows at 1e-10 of a refined result. (FP64
+// results keep 1e-14 at any rows: the interface factors are formed without
+// cancellation.)
 int builtin_shape(Plan& p) {
     PSV_HIP(hipGetDevice(&p.device));
     int lds_max = 0;
