@@ -841,7 +841,10 @@ __device__ __forceinline__ void ifc_table_pair(const ZArgs& z, int s, T* tab) {
             // a + cc = u + eu, b0 + lam = b + eb, exactly
             const double u = a + cc, ua = u - a, eu = (a - (u - ua)) + (cc - ua);
             const double b = b0 + lam, bl = b - b0, eb = (b0 - (b - bl)) + (lam - bl);
-            const double sg = ((eb - eu) - (u + b0)) - lam;  // -(a + b + cc)
+            double sg = ((eb - eu) - (u + b0)) - lam;  // -(a + b + cc)
+            // where lam vanishes in b the rounded rows are singular (a domain 1e-8 thick)
+            // and no FP64 solve of theirs is accurate; the factors stay finite
+            if (!(sg > 0.0)) sg = -lam;
             if (i < 2) {
                 const double r = rcp_nr(-b);
                 q[i] = Row{a * r, cc * r, sg * r};

@@ -50,3 +50,20 @@ def test_lowest_mode(gpu, ny, nz, lz, stretch):
         err = rel_max_err(host(plan.solve(dev(f))), ref)
         say(f"{nx}x{ny}x{nz} lz {lz} chunk rows {kc}: {err:.2e}")
         assert err <= (2 * nz / kc + kc) * 2.0 ** -52 + 1e-14, (kc, err)
+
+
+@pytest.mark.parametrize("ny,nz", [(4, 64), (16, 37), (1, 50)])
+def test_eigenvalue_below_the_rounding_of_the_diagonal(gpu, ny, nz):
+    """A domain 1e-8 thick: the lowest modes' eigenvalue sums vanish in the diagonals
+    of the wall-normal systems, which are then singular as rounded. Their part of the
+    result hangs on rounding, but no factor is infinite and the result is finite."""
+    nx = 16
+    x = np.cos(2 * np.pi * (np.arange(nx) + 0.5) / nx)
+    f = np.broadcast_to(x, (nz, ny, nx)).copy()
+    for prec in ("fp64", "mixed"):
+        plan = gpu.Plan(gpu.Grid(nx, ny, nz, 1.0, 1.0, 1e-8), method="const", precision=prec)
+        for kc in (4, 8, 16):
+            plan.set_shape(chunk_rows=kc)
+            p = host(plan.solve(dev(f)))
+            say(f"thin {prec} {nx}x{ny}x{nz} chunk rows {kc}: {np.abs(p).max():.2e}")
+            assert np.isfinite(p).all()
